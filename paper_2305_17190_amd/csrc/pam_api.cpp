@@ -71,11 +71,16 @@ constexpr int kSimdsPerCu = 4;
 // relative to four: one wave issues alone, two pair their adds and fmas
 // but leave barrier and LDS waits exposed.
 constexpr double kSimdEfficiency[5] = {0.0, 0.4495, 0.8693, 0.8743, 1.0};
-constexpr double kWorkgroupFixedS = 3.15e-6;  // first loads, epilogue stores
-constexpr double kSplitFixedS = 12.7e-6;      // second launch, workspace
-// Effective rate of writing and re-reading partial sums: up to a few hundred
-// MB they largely stay in the last-level cache, so above the HBM rate.
-constexpr double kPartialBytesPerS = 24.7e12;
+// Costs beside the chunks: a workgroup's first loads and epilogue stores; a
+// split's second launch; the effective rate of writing and re-reading
+// partial sums (matrix products: up to a few hundred MB they largely stay in
+// the last-level cache, so above the HBM rate).
+struct Costs {
+    double workgroup_s;
+    double split_s;
+    double partial_bytes_per_s;
+};
+const Costs kGemmCosts = {3.15e-6, 12.7e-6, 24.7e12};
 // Workgroups start as soon as slots free up, so a partial last round costs
 // less than a full one the more rounds precede it (they end staggered).
 constexpr double kTailDamping = 0.925;
@@ -144,22 +149,23 @@ double rounds_time(const Shape &c, int64_t wgs, double wg_s, int64_t before) {
 // slices of the split tiles together with the whole-K tiles of a partial
 // round (counted as the slices they displace), plus for split-K a second
 // launch and the partial sums' round trip through memory.
-double plan_time(const Shape &c, const Plan &p, int64_t m, int64_t n, int64_t k, int64_t batch) {
+double plan_time(const Shape &c, const Plan &p, int64_t m, int64_t n, int64_t k, int64_t batch,
+                 const Costs &costs = kGemmCosts) {
     const int64_t bk = pamk::kChunkK * c.kw;
     const int64_t slots = (int64_t)c.per_cu * kComputeUnits;
     const int64_t tiles = ceil_div(m, c.bm) * ceil_div(n, c.bn) * batch;
     const double per_chunk = double(c.bm) * c.bn * bk * slots / c.rate;
-    const double wg_whole = per_chunk * double(ceil_div(k, bk)) + kWorkgroupFixedS;
+    const double wg_whole = per_chunk * double(ceil_div(k, bk)) + costs.workgroup_s;
     if (p.splits <= 1)
         return rounds_time(c, tiles, wg_whole, 0);
     const int64_t whole = std::min(p.whole_tiles, tiles);
     const int64_t split_tiles = tiles - whole;
     const int64_t before = whole / slots;
     const int64_t rem = whole % slots;
-    const double wg_slice = per_chunk * double(ceil_div(p.k_per_split, bk)) + kWorkgroupFixedS;
+    const double wg_slice = per_chunk * double(ceil_div(p.k_per_split, bk)) + costs.workgroup_s;
     const int64_t displaced = rem > 0 ? (int64_t)std::ceil(double(rem) * wg_whole / wg_slice) : 0;
     double t = double(before) * wg_whole + rounds_time(c, split_tiles * p.splits + displaced, wg_slice, before);
-    t += kSplitFixedS + double(p.splits + 1) * double(split_tiles) * c.bm * c.bn * 4.0 / kPartialBytesPerS;
+    t += costs.split_s + double(p.splits + 1) * double(split_tiles) * c.bm * c.bn * 4.0 / costs.partial_bytes_per_s;
     return t;
 }
 
@@ -485,24 +491,55 @@ int query_simds_per_cu(int device) {
     return ctx.simds;
 }
 
-// Exact-derivative products: 128 x 128 tiles, two workgroups per compute
-// unit; K is split while the tiles would not fill two rounds and each slice
-// keeps >= 4 chunks.  Partial sums [split][m][n].
-int64_t exact_grad_splits(int64_t m, int64_t n, int64_t k) {
-    const int64_t tiles = ceil_div(m, 128) * ceil_div(n, 128);
-    int64_t splits = 1;
-    while (tiles * splits < 4 * kComputeUnits && splits < kMaxSplits && k / (splits * 2) >= 4 * pamk::kChunkK)
-        splits *= 2;
-    return splits;
-}
+// Exact-derivative products: one tile shape.  Fitted to sweeps of the split
+// count (a round's workgroups read and write their 32 KB tiles of Mod and
+// of partial sums all at once: about 13 us beside 6.4 us a chunk; the reduce
+// ran at 5.5 TB/s).
+const Shape kExactShape = {pamk::kExactTileM, pamk::kExactTileN, 1, 4, 4, 21.0e12};
+const Costs kExactCosts = {13e-6, 3e-6, 5.5e12};
 
-size_t exact_grad_workspace(int64_t m, int64_t n, int64_t k, int64_t *splits_out, int64_t *per_out) {
-    const int64_t splits = exact_grad_splits(m, n, k);
-    const int64_t per = ceil_div(ceil_div(k, splits), pamk::kChunkK) * pamk::kChunkK;
-    const int64_t used = ceil_div(k, per);
-    *splits_out = used;
-    *per_out = per;
-    return used > 1 ? (size_t)used * (size_t)m * (size_t)n * sizeof(float) : 0;
+// The plan of an exact-derivative product: K kept whole, or, with a workspace
+// and unless the tiles make two or more full rounds exactly, the cheapest of
+// the split counts and hybrids that choose_plan considers for a tile shape.
+// While 1024 tiles of 128 x 128 are not reached, K is split (into slices of
+// at least four chunks) until tiles x slices about reach them: the shorter
+// sums keep the rounding error of a long K down (8192 x 512 and 2048 x 512
+// outputs over K = 2048 and 8192: 3.7e-7 of the result with 4 and 16 slices,
+// 5.8e-7 with 2 and 8) and cost nothing (486 / 454 us against 560 / 463).
+Plan choose_exact_plan(int64_t m, int64_t n, int64_t k, bool split_ok) {
+    const Shape &c = kExactShape;
+    Plan best = make_plan(c, k, 1);
+    const int64_t slots = (int64_t)c.per_cu * kComputeUnits;
+    const int64_t tiles = ceil_div(m, c.bm) * ceil_div(n, c.bn);
+    const int64_t rest = tiles % slots;
+    if (!split_ok || (rest == 0 && tiles >= 2 * slots) || tiles > kMaxHybridTiles)
+        return best;
+    const int64_t most = std::max<int64_t>(1, std::min(kMaxSplits, k / (4 * pamk::kChunkK)));
+    const int64_t squares = ceil_div(m, 128) * ceil_div(n, 128);
+    int64_t least = 1;
+    while (squares * least < 1024 && 2 * least <= most)
+        least *= 2;
+    bool have = least == 1;
+    double best_t = kSplitMargin * plan_time(c, best, m, n, k, 1, kExactCosts);
+    for (const int s : kSplitChoices) {
+        if (s == 1 || 8 * s < 7 * least)
+            continue;
+        if (s > most)
+            break;
+        const int64_t tails[3] = {tiles, least > 1 ? 0 : rest, least > 1 ? 0 : rest + slots};
+        for (const int64_t tail : tails) {
+            if (tail <= 0 || tail > tiles)
+                continue;
+            const Plan p = make_plan(c, k, s, tiles - tail);
+            const double t = plan_time(c, p, m, n, k, 1, kExactCosts);
+            if (!have || t < best_t) {
+                have = true;
+                best_t = t;
+                best = p;
+            }
+        }
+    }
+    return best;
 }
 
 // ext == nullptr: one K slice (no workspace); otherwise the split plan, its
@@ -519,11 +556,13 @@ pam_status_t run_exact_grad(pam_op_t transA, int64_t m, int64_t n, int64_t k, co
         return PAM_SUCCESS;
     if (Mod == nullptr)
         return fail(PAM_ERROR_INVALID_VALUE, "Mod is NULL");
-    int64_t splits = 1, per = std::max<int64_t>(k, 1);
-    size_t need = 0;
-    if (k > 0 && ext != nullptr)
-        need = exact_grad_workspace(m, n, k, &splits, &per);
-    st = check_workspace(ext, need);
+    const Plan plan = choose_exact_plan(m, n, k, ext != nullptr);
+    Layout L{};
+    st = layout_of(plan, m, n, 1, &L);
+    if (st != PAM_SUCCESS)
+        return st;
+    if (k > 0)
+        st = check_workspace(ext, L.ws_bytes);
     if (st != PAM_SUCCESS)
         return st;
     st = check_device();
@@ -544,19 +583,23 @@ pam_status_t run_exact_grad(pam_op_t transA, int64_t m, int64_t n, int64_t k, co
     p.m = (int32_t)m;
     p.n = (int32_t)n;
     p.k = (int32_t)k;
-    p.k_per_split = (int32_t)std::min<int64_t>(per, kMaxDim);
-    p.splits = (int32_t)splits;
-    p.tiles_n = (int32_t)ceil_div(n, 128);
+    p.k_per_split = (int32_t)std::min<int64_t>(plan.k_per_split, kMaxDim);
+    p.splits = (int32_t)L.splits;
+    p.tiles = (int32_t)L.tiles;
+    p.tiles_n = (int32_t)ceil_div(n, plan.tile_n);
+    p.whole = (int32_t)(L.splits > 1 ? L.whole_tiles : L.tiles);
+    p.split_tiles = (int32_t)(L.tiles - p.whole);
     p.vec_a = aligned16(A) && lda % 4 == 0;
     p.vec_b = aligned16(B) && ldb % 4 == 0;
-    float *ws = need > 0 ? static_cast<float *>(ext->ptr) : nullptr;
+    p.vec_c = aligned16(C) && ldc % 4 == 0;
+    p.vec_mod = aligned16(Mod) && ldm % 4 == 0;
     p.C = C;
-    p.W = ws;
+    p.W = L.ws_bytes > 0 ? static_cast<float *>(ext->ptr) : nullptr;
     hipError_t e = pamk::launch_pam_exact_grad(transA == PAM_OP_T, p, stream);
     if (e != hipSuccess)
         return fail_hip(e, "exact-derivative kernel launch");
-    if (ws) {
-        e = pamk::launch_splitk_reduce(ws, C, (int32_t)m, (int32_t)n, ldc, 0, p.splits, 1, stream);
+    if (p.split_tiles > 0) {
+        e = pamk::launch_split_tile_reduce(plan.tile_m, plan.tile_n, p, stream);
         if (e != hipSuccess)
             return fail_hip(e, "split-K reduce launch");
     }
@@ -799,8 +842,11 @@ pam_status_t pam_gemm_exact_grad_workspace_size(int64_t m, int64_t n, int64_t k,
         return fail(PAM_ERROR_INVALID_VALUE, "m, n and k must be below 2^31");
     if (m == 0 || n == 0 || k == 0)
         return PAM_SUCCESS;
-    int64_t splits, per;
-    *bytes = exact_grad_workspace(m, n, k, &splits, &per);
+    Layout L;
+    const pam_status_t st = layout_of(choose_exact_plan(m, n, k, true), m, n, 1, &L);
+    if (st != PAM_SUCCESS)
+        return st;
+    *bytes = L.ws_bytes;
     return PAM_SUCCESS;
 }
 

@@ -26,25 +26,37 @@
 //   * b that is normal but not safe ("extreme"): staged as 0 for the fast
 //     path, and the LDS chunk's steps holding one are flagged; in a flagged
 //     step each thread adds the general term for its columns whose b is
-//     extreme.
+//     extreme (a second plane of B keeps the extreme values).
 //   * mod that is normal but not safe: the output's fast-path sum is
 //     discarded; the workgroup lists such outputs in LDS (up to 512 of the
-//     tile's 16384) and deals them out evenly over its threads, each keeping
+//     tile's 8192) and deals them out evenly over its threads, each keeping
 //     the sums of at most two, over every k with the general term.  A tile
 //     with more takes the general term for every term.
 //   * zero / denormal mod: the output is zero.
-// The general term needs mod's exponent field, kept for the whole tile in
-// LDS as bytes; mod's mantissa stays in registers for the fast path.
+// The general term needs mod's exponent; mod's mantissa stays in registers
+// for the fast path, so flagged steps read mod again from memory.
 //
-// Tiling: 128 x 128 output tile per 256-thread workgroup, 8 x 8 register
-// micro-tiles, K in LDS chunks of 16; split-K into the workspace p.W when
-// several K slices run.
+// What bounds it: vector-ALU issue, three full-rate ops per term (v_and_b32
+// with register operands issues at the rate of the adds; with a scalar
+// register operand at half of it).  The bare three-op sequence ran at
+// 22.4e12 terms/s over the whole chip.  Tiling: 128 x 64 outputs per
+// 256-thread workgroup, 8 x 4 register micro-tiles: accumulators and mod
+// mantissas together take 64 registers, so four waves fit a SIMD (an 8 x 8
+// micro-tile takes 128 and left two).  Chunks of 16 k steps are copied into
+// LDS by the memory pipeline while the previous one is computed
+// (pam_dma_tile.h), and each step's operands are read one step ahead.
+// Measured, with the reduction of the K slices, against the earlier kernel
+// (128 x 128 tiles staged through registers, two waves per SIMD): 8192 x 512
+// outputs over K = 2048 486 us (628 us), 2048 x 512 over K = 8192 454 us (623),
+// 12608 x 192 over K = 768 133 us (366), 768 x 192 over K = 12608 122 us (301),
+// 4096 x 4096 x 4096 19.5e12 terms/s.  What is left over the chunks is a
+// workgroup's Mod tile read and its output written, 13 us a round.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pam_dma_tile.h"
 #include "pam_internal.h"
-#include "pam_tile.h"
 
 namespace pamk {
 namespace {
@@ -76,117 +88,92 @@ __device__ __forceinline__ void general_fma(float &acc, float a, uint32_t b, uin
     acc = fmaf(a2, __uint_as_float(g), acc);
 }
 
-// Raw operand words into one k-major LDS plane s[kk][o].
-template <int LDS_LD, int D, int NT, int BK, bool KCONTIG>
-__device__ __forceinline__ void store_a(const TileLoader<D, NT, BK, KCONTIG> &ld, uint32_t (*s)[LDS_LD], int tid) {
-    using TL = TileLoader<D, NT, BK, KCONTIG>;
-#pragma unroll
-    for (int r = 0; r < TL::L; ++r) {
-        const uint32_t e[4] = {ld.v[r].x, ld.v[r].y, ld.v[r].z, ld.v[r].w};
-        const int o = TL::grp_o(tid, r);
-        const int kk = TL::grp_k(tid, r);
-        if (KCONTIG) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                s[kk + c][o] = e[c];
-        } else {
-            *reinterpret_cast<uint4 *>(&s[kk][o]) = make_uint4(e[0], e[1], e[2], e[3]);
-        }
-    }
-}
+// One k step of the micro-tile, acc[i][j] += a_i * ((b_j + mm[i][j]) & sign and
+// exponent), two rows at a time: eight independent ops of each kind.
+#define PAM_EXACT_ROWS(R, S, A, B)                                                                              \
+    "v_add_u32 %[t0], %[m" #R "0], %[b0]\n\tv_add_u32 %[t1], %[m" #R "1], %[b1]\n\t"                           \
+    "v_add_u32 %[t2], %[m" #R "2], %[b2]\n\tv_add_u32 %[t3], %[m" #R "3], %[b3]\n\t"                           \
+    "v_add_u32 %[t4], %[m" #S "0], %[b0]\n\tv_add_u32 %[t5], %[m" #S "1], %[b1]\n\t"                           \
+    "v_add_u32 %[t6], %[m" #S "2], %[b2]\n\tv_add_u32 %[t7], %[m" #S "3], %[b3]\n\t"                           \
+    "v_and_b32 %[t0], %[se], %[t0]\n\tv_and_b32 %[t1], %[se], %[t1]\n\t"                                     \
+    "v_and_b32 %[t2], %[se], %[t2]\n\tv_and_b32 %[t3], %[se], %[t3]\n\t"                                     \
+    "v_and_b32 %[t4], %[se], %[t4]\n\tv_and_b32 %[t5], %[se], %[t5]\n\t"                                     \
+    "v_and_b32 %[t6], %[se], %[t6]\n\tv_and_b32 %[t7], %[se], %[t7]\n\t"                                     \
+    "v_fmac_f32 %[c" #R "0], %[" #A "], %[t0]\n\tv_fmac_f32 %[c" #R "1], %[" #A "], %[t1]\n\t"                 \
+    "v_fmac_f32 %[c" #R "2], %[" #A "], %[t2]\n\tv_fmac_f32 %[c" #R "3], %[" #A "], %[t3]\n\t"                 \
+    "v_fmac_f32 %[c" #S "0], %[" #B "], %[t4]\n\tv_fmac_f32 %[c" #S "1], %[" #B "], %[t5]\n\t"                 \
+    "v_fmac_f32 %[c" #S "2], %[" #B "], %[t6]\n\tv_fmac_f32 %[c" #S "3], %[" #B "], %[t7]\n\t"
+#define PAM_EXACT_ACC(R)                                                                                        \
+    [c##R##0] "+v"(acc[R][0]), [c##R##1] "+v"(acc[R][1]), [c##R##2] "+v"(acc[R][2]), [c##R##3] "+v"(acc[R][3])
+#define PAM_EXACT_MOD(R)                                                                                        \
+    [m##R##0] "v"(mm[R][0]), [m##R##1] "v"(mm[R][1]), [m##R##2] "v"(mm[R][2]), [m##R##3] "v"(mm[R][3])
 
-// B (k-major in memory, rows kk, columns o) into two planes: plane 0 for the
-// fast path (zero, denormal and extreme b as 0), plane 1 for the general
-// term (zero and denormal b as 0, extreme b kept); a chunk step holding an
-// extreme b sets its bit in *slow.
-template <int LDS_LD, int D, int NT, int BK>
-__device__ __forceinline__ void store_b(const TileLoader<D, NT, BK, false> &ld, uint32_t (*s)[BK][LDS_LD], int tid,
-                                        uint32_t *slow) {
-    using TL = TileLoader<D, NT, BK, false>;
-#pragma unroll
-    for (int r = 0; r < TL::L; ++r) {
-        const uint32_t e[4] = {ld.v[r].x, ld.v[r].y, ld.v[r].z, ld.v[r].w};
-        uint32_t fast[4], full[4];
-        bool any = false;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const uint32_t u = e[c];
-            const bool zero = (u & kExpMask) == 0u;
-            const bool ext = extreme(u);
-            full[c] = zero ? 0u : u;
-            fast[c] = (zero || ext) ? 0u : u;
-            any = any || ext;
-        }
-        const int o = TL::grp_o(tid, r);
-        const int kk = TL::grp_k(tid, r);
-        *reinterpret_cast<uint4 *>(&s[0][kk][o]) = make_uint4(fast[0], fast[1], fast[2], fast[3]);
-        *reinterpret_cast<uint4 *>(&s[1][kk][o]) = make_uint4(full[0], full[1], full[2], full[3]);
-        if (any)
-            atomicOr(slow, 1u << kk);
-    }
-}
-
-// One micro-tile row: acc[j] += a * ((b[j] + mm[j]) & sign|exponent).
-__device__ __forceinline__ void exact_row(float (&acc)[8], float a, const uint32_t (&b)[8], const uint32_t (&mm)[8]) {
+__device__ __forceinline__ void exact_step(float (&acc)[8][4], const uint32_t (&mm)[8][4], const uint4 &al,
+                                           const uint4 &ah, const uint4 &b, uint32_t sign_exp) {
     uint32_t t0, t1, t2, t3, t4, t5, t6, t7;
-    asm("v_add_u32 %0, %17, %25\n\t"
-        "v_add_u32 %1, %18, %26\n\t"
-        "v_add_u32 %2, %19, %27\n\t"
-        "v_add_u32 %3, %20, %28\n\t"
-        "v_add_u32 %4, %21, %29\n\t"
-        "v_add_u32 %5, %22, %30\n\t"
-        "v_add_u32 %6, %23, %31\n\t"
-        "v_add_u32 %7, %24, %32\n\t"
-        "v_and_b32 %0, 0xff800000, %0\n\t"
-        "v_and_b32 %1, 0xff800000, %1\n\t"
-        "v_and_b32 %2, 0xff800000, %2\n\t"
-        "v_and_b32 %3, 0xff800000, %3\n\t"
-        "v_and_b32 %4, 0xff800000, %4\n\t"
-        "v_and_b32 %5, 0xff800000, %5\n\t"
-        "v_and_b32 %6, 0xff800000, %6\n\t"
-        "v_and_b32 %7, 0xff800000, %7\n\t"
-        "v_fmac_f32 %8, %16, %0\n\t"
-        "v_fmac_f32 %9, %16, %1\n\t"
-        "v_fmac_f32 %10, %16, %2\n\t"
-        "v_fmac_f32 %11, %16, %3\n\t"
-        "v_fmac_f32 %12, %16, %4\n\t"
-        "v_fmac_f32 %13, %16, %5\n\t"
-        "v_fmac_f32 %14, %16, %6\n\t"
-        "v_fmac_f32 %15, %16, %7"
-        : "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3), "=&v"(t4), "=&v"(t5), "=&v"(t6), "=&v"(t7),
-          "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
-          "+v"(acc[7])
-        : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]),
-          "v"(mm[0]), "v"(mm[1]), "v"(mm[2]), "v"(mm[3]), "v"(mm[4]), "v"(mm[5]), "v"(mm[6]), "v"(mm[7]));
+    asm(PAM_EXACT_ROWS(0, 1, a0, a1) PAM_EXACT_ROWS(2, 3, a2, a3) PAM_EXACT_ROWS(4, 5, a4, a5)
+            PAM_EXACT_ROWS(6, 7, a6, a7)
+        : PAM_EXACT_ACC(0), PAM_EXACT_ACC(1), PAM_EXACT_ACC(2), PAM_EXACT_ACC(3), PAM_EXACT_ACC(4), PAM_EXACT_ACC(5),
+          PAM_EXACT_ACC(6), PAM_EXACT_ACC(7), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3),
+          [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6), [t7] "=&v"(t7)
+        : PAM_EXACT_MOD(0), PAM_EXACT_MOD(1), PAM_EXACT_MOD(2), PAM_EXACT_MOD(3), PAM_EXACT_MOD(4), PAM_EXACT_MOD(5),
+          PAM_EXACT_MOD(6), PAM_EXACT_MOD(7), [a0] "v"(al.x), [a1] "v"(al.y), [a2] "v"(al.z), [a3] "v"(al.w),
+          [a4] "v"(ah.x), [a5] "v"(ah.y), [a6] "v"(ah.z), [a7] "v"(ah.w), [b0] "v"(b.x), [b1] "v"(b.y), [b2] "v"(b.z),
+          [b3] "v"(b.w), [se] "v"(sign_exp));
+}
+#undef PAM_EXACT_ROWS
+#undef PAM_EXACT_ACC
+#undef PAM_EXACT_MOD
+
+// Four words of a row of Mod from column col (zero past n).
+__device__ __forceinline__ uint4 mod_quad(const float *row, int col, int n, bool vec) {
+    if (vec && col + 3 < n)
+        return *reinterpret_cast<const uint4 *>(row + col);
+    uint32_t u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        u[j] = col + j < n ? __float_as_uint(row[col + j]) : 0u;
+    return make_uint4(u[0], u[1], u[2], u[3]);
 }
 
 template <bool TA>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 pam_exact_grad_kernel(GemmParams p) {
-    constexpr int BM = 128, BN = 128, BK = kChunkK;
+    constexpr int BM = kExactTileM, BN = kExactTileN, BK = kChunkK;
     constexpr int NT = 256;
-    constexpr int TXN = BN / 8;
-    constexpr int HM = BM / 2, HN = BN / 2;
-    constexpr int LDA = BM + 4, LDB = BN + 4;
-    constexpr int LDE = BN / 4 + 1;   // words per row of the Mod exponent bytes
-    __shared__ __attribute__((aligned(16))) uint32_t sA[BK][LDA];
-    __shared__ __attribute__((aligned(16))) uint32_t sB[2][BK][LDB];
+    constexpr int HM = BM / 2;
+    using TileA = DmaTile<BM, BK, NT, !TA, float>;
+    using TileB = DmaTile<BN, BK, NT, false, float>;
+    constexpr int kRawA = TileA::CL * NT * 4;
+    constexpr int kRawB = TileB::CL * NT * 4;
     constexpr int kListCap = 2 * NT;   // extreme-Mod outputs a tile lists
-    __shared__ uint32_t sE[BM][LDE];   // Mod exponent fields, four columns per word
+    __shared__ __attribute__((aligned(16))) uint32_t smem[kRawA + kRawB + BK * BM + 2 * BK * BN];
     __shared__ uint32_t sSlow[2];      // [chunk parity] steps holding an extreme b
     __shared__ uint32_t sCount;        // extreme-Mod outputs of the tile
     __shared__ uint32_t sList[2][kListCap];   // their (row << 16 | column) and Mod words
+    uint32_t *rawA = smem;
+    uint32_t *rawB = smem + kRawA;
+    uint32_t *sA = smem + kRawA + kRawB;   // A as it is, k-major
+    uint32_t *sB = sA + BK * BM;           // B with zero, denormal and extreme values as 0
+    uint32_t *sBx = sB + BK * BN;          // B with zero and denormal values as 0
 
     const int tid = threadIdx.x;
-    const int tx = tid % TXN;
-    const int ty = tid / TXN;
-    const int tm = blockIdx.x / p.tiles_n;
-    const int tn = blockIdx.x % p.tiles_n;
-    const int m0 = tm * BM;
-    const int n0 = tn * BN;
-    const int split = blockIdx.y;
-    const int kb = split * p.k_per_split;
-    const int ke = min(p.k, kb + p.k_per_split);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t lds_w = __builtin_amdgcn_readfirstlane(lds_addr(smem) + (uint32_t)wave * 1024u);
+    const int lane = tid & 63;
+    const int tx = (wave % 2) * 8 + (lane & 7);
+    const int ty = (wave / 2) * 8 + (lane >> 3);
+    const uint32_t item = blockIdx.x;
+    const bool whole = item < (uint32_t)p.whole;
+    const uint32_t rel = item - (uint32_t)p.whole;
+    const uint32_t nsplit = (uint32_t)max(p.split_tiles, 1);
+    const uint32_t st = whole ? 0u : rel % nsplit;
+    const int split = whole ? 0 : (int)(rel / nsplit);
+    const uint32_t tile = whole ? item : (uint32_t)p.whole + st;
+    const int m0 = (int)(tile / (uint32_t)p.tiles_n) * BM;
+    const int n0 = (int)(tile % (uint32_t)p.tiles_n) * BN;
+    const int kb = whole ? 0 : split * p.k_per_split;
+    const int ke = whole ? p.k : min(p.k, kb + p.k_per_split);
     const int nchunks = ke > kb ? (ke - kb + BK - 1) / BK : 0;
 
     // op(A) rows m0.. and B columns n0.. (B is k-major: B[q * ldb + c]).
@@ -194,105 +181,163 @@ pam_exact_grad_kernel(GemmParams p) {
     const float *b_base = p.B + (int64_t)kb * p.ldb + n0;
     const int64_t a_step = TA ? (int64_t)BK * p.lda : BK;
     const int64_t b_step = (int64_t)BK * p.ldb;
-    const bool vec_a = p.vec_a != 0;
-    const bool vec_b = p.vec_b != 0;
+    const uint32_t flags = (p.vec_a != 0 ? 1u : 0u) | (p.vec_b != 0 ? 2u : 0u);
 
-    TileLoader<BM, NT, BK, !TA> la;
-    TileLoader<BN, NT, BK, false> lb;
-    la.init(p.lda, m0, p.m, tid);
-    lb.init(p.ldb, n0, p.n, tid);
-
+    if (kb + BK <= ke) {
+        if (p.vec_a != 0)
+            TileA::template copy<0>(a_base, lds_w, tid, p.lda, m0, p.m);
+        if (p.vec_b != 0)
+            TileB::template copy<kRawA * 4>(b_base, lds_w, tid, p.ldb, n0, p.n);
+    }
     if (tid < 2)
         sSlow[tid] = 0u;
     if (tid == 0)
         sCount = 0u;
     __syncthreads();
 
-    // The micro-tile's Mod mantissas, fixed for the whole K loop, and its
-    // exponent fields in LDS; outputs with an extreme Mod go to the tile's
-    // list.
-    uint32_t mm[8][8];
+    // The micro-tile's Mod words.  One bit per output (4 i + j): its Mod is zero
+    // or denormal; its Mod is extreme (then it goes to the tile's list).
+    const int c0 = tx * 4;                                                  // first tile column
+    uint32_t mm[8][4];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int lr = i < 4 ? ty * 4 + i : HM + ty * 4 + (i - 4);
-        const int row = m0 + lr;
+        uint4 q = make_uint4(0u, 0u, 0u, 0u);
+        if (m0 + lr < p.m)
+            q = mod_quad(p.Mod + (int64_t)(m0 + lr) * p.ldm, n0 + c0, p.n, p.vec_mod != 0);
+        mm[i][0] = q.x;
+        mm[i][1] = q.y;
+        mm[i][2] = q.z;
+        mm[i][3] = q.w;
+    }
+    uint32_t zero_mod = 0u, extreme_mod = 0u;
+    uint32_t least = 0xFFFFFFFFu, most = 0u;   // exponent fields in the top byte
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            uint32_t fields = 0u;
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int j = 4 * h + jj;
-                const int lc = (h == 0 ? tx * 4 : HN + tx * 4) + jj;
-                const int col = n0 + lc;
-                uint32_t u = 0u;
-                if (row < p.m && col < p.n)
-                    u = __float_as_uint(p.Mod[(int64_t)row * p.ldm + col]);
-                // kept as computed: re-deriving it inside the loop would cost
-                // an op per term
-                asm volatile("v_and_b32 %0, 0x7fffff, %1" : "=v"(mm[i][j]) : "v"(u));
-                fields |= ((u >> 23) & 0xFFu) << (8 * jj);
+        for (int j = 0; j < 4; ++j) {
+            least = min(least, mm[i][j] << 1);
+            most = max(most, mm[i][j] << 1);
+        }
+    if (least < (kSafeLo << 24) || most >= ((kSafeHi + 1u) << 24)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t u = mm[i][j];
+                zero_mod |= (u & kExpMask) == 0u ? 1u << (4 * i + j) : 0u;
                 if (extreme(u)) {
+                    extreme_mod |= 1u << (4 * i + j);
                     const uint32_t e = atomicAdd(&sCount, 1u);
                     if (e < (uint32_t)kListCap) {
-                        sList[0][e] = ((uint32_t)lr << 16) | (uint32_t)lc;
+                        const int lr = i < 4 ? ty * 4 + i : HM + ty * 4 + (i - 4);
+                        sList[0][e] = ((uint32_t)lr << 16) | (uint32_t)(c0 + j);
                         sList[1][e] = u;
                     }
                 }
             }
-            sE[lr][(h == 0 ? tx : HN / 4 + tx)] = fields;
-        }
     }
-
-    float acc[8][8];
+    __syncthreads();
+    const uint32_t nlist = __builtin_amdgcn_readfirstlane(sCount);
+    const bool dense = nlist > (uint32_t)kListCap;
+    // The fast path takes the mantissas alone (a dense tile the whole words).
+    uint32_t keep = dense ? 0xFFFFFFFFu : kMant;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+        for (int j = 0; j < 4; ++j)
+            // kept as computed: re-deriving it inside the loop would cost an
+            // op per term
+            asm volatile("v_and_b32 %0, %1, %0" : "+v"(mm[i][j]) : "v"(keep));
+
+    float acc[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
             acc[i][j] = 0.0f;
 
-    if (nchunks > 0) {
-        la.load(a_base, m0, p.m, kb, ke, vec_a, tid);
-        lb.load(b_base, n0, p.n, kb, ke, vec_b, tid);
-    }
-    __syncthreads();
-    const uint32_t nlist = sCount;
-    const bool dense = nlist > (uint32_t)kListCap;
     // This thread's list entries: e = s * NT + slot(tid), slots dealt so that
     // consecutive entries go to different waves.
-    const uint32_t slot = (uint32_t)((tid % 64) * (NT / 64) + tid / 64);
-    uint32_t side_rc[2], side_mod[2];
+    const uint32_t slot = (uint32_t)(lane * (NT / 64) + wave);
+    const uint32_t nside = dense ? 0u : nlist;   // the same for the whole workgroup
     float side_acc[2] = {0.0f, 0.0f};
-    bool side_on[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const uint32_t idx = (uint32_t)e * NT + slot;
-        side_on[e] = !dense && idx < nlist;
-        side_rc[e] = side_on[e] ? sList[0][idx] : 0u;
-        side_mod[e] = side_on[e] ? sList[1][idx] : 0u;
-    }
 
+    TileA la;
+    TileB lb;
     for (int c = 0; c < nchunks; ++c) {
+        const int k0 = kb + c * BK;
+        const bool interior = k0 + BK <= ke;
+        uint32_t fl = __builtin_amdgcn_readfirstlane(flags);
+        asm volatile("" : "+s"(fl));
+        // Staging addresses are recomputed per chunk from the thread index
+        // instead of staying in registers across the steps.
+        int tid_c = tid;
+        asm volatile("" : "+v"(tid_c));
+        __builtin_amdgcn_s_setprio(1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's copies of chunk c have landed
+        la.fetch(rawA, wave, tid_c & 63, interior && (fl & 1u), a_base + c * a_step, p.lda, m0, p.m, k0, ke, tid_c);
+        lb.fetch(rawB, wave, tid_c & 63, interior && (fl & 2u), b_base + c * b_step, p.ldb, n0, p.n, k0, ke, tid_c);
+        uint32_t smin[TileB::L];
+        const uint32_t mx = lb.scan(smin);
+        static_assert(TileB::L == 1, "one B segment per thread");
+        const bool odd = TileB::low_seg(smin[0]) || mx >= (191u << 24);   // a zero, denormal or extreme b
         __syncthreads();   // every wave is done reading the previous chunk
-        store_a<LDA>(la, sA, tid);
-        store_b<LDB>(lb, sB, tid, &sSlow[c & 1]);
+        la.store_values(sA, false, tid_c);
+        uint4 fast = lb.v[0], full = lb.v[0];
+        if (odd) {
+            const uint32_t e[4] = {lb.v[0].x, lb.v[0].y, lb.v[0].z, lb.v[0].w};
+            uint32_t f0[4], f1[4];
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool zero = (e[j] & kExpMask) == 0u;
+                const bool ext = extreme(e[j]);
+                f1[j] = zero ? 0u : e[j];
+                f0[j] = (zero || ext) ? 0u : e[j];
+                any = any || ext;
+            }
+            fast = make_uint4(f0[0], f0[1], f0[2], f0[3]);
+            full = make_uint4(f1[0], f1[1], f1[2], f1[3]);
+            if (any)
+                atomicOr(&sSlow[c & 1], 1u << TileB::seg_k(tid_c, 0));
+        }
+        const int b_at = TileB::seg_k(tid_c, 0) * BN + TileB::seg_o(tid_c, 0);
+        *reinterpret_cast<uint4 *>(sB + b_at) = fast;
+        *reinterpret_cast<uint4 *>(sBx + b_at) = full;
         __syncthreads();
         const uint32_t slow = __builtin_amdgcn_readfirstlane(sSlow[c & 1]);
         if (tid == 0)
             sSlow[(c + 1) & 1] = 0u;   // next chunk's flags; last read one chunk ago
-        if (c + 1 < nchunks) {
-            const int k0 = kb + (c + 1) * BK;
-            la.load(a_base + (c + 1) * a_step, m0, p.m, k0, ke, vec_a, tid);
-            lb.load(b_base + (c + 1) * b_step, n0, p.n, k0, ke, vec_b, tid);
+        // The next chunk's copies land while this one is computed.
+        if (c + 1 < nchunks && k0 + 2 * BK <= ke) {
+            if (fl & 1u)
+                TileA::template copy<0>(a_base + (c + 1) * a_step, lds_w, tid_c, p.lda, m0, p.m);
+            if (fl & 2u)
+                TileB::template copy<kRawA * 4>(b_base + (c + 1) * b_step, lds_w, tid_c, p.ldb, n0, p.n);
         }
+        __builtin_amdgcn_s_setprio(0);
+
         if (!dense) {
-#pragma unroll 1
-            for (int kk = 0; kk < BK; ++kk) {
-                uint32_t av[8], bv[8];
-                lds_frag<BK, LDA>(&sA, 0, kk, ty * 4, HM, av);
-                lds_frag<BK, LDB>(sB, 0, kk, tx * 4, HN, bv);
+            const uint32_t *a_row = sA + ty * 4;
+            const uint32_t *b_row = sB + c0;
+            uint4 al[2], ah[2], bq[2];
+            auto rd = [&](int k, int s) {
+                al[s] = *reinterpret_cast<const uint4 *>(a_row + k * BM);
+                ah[s] = *reinterpret_cast<const uint4 *>(a_row + k * BM + HM);
+                bq[s] = *reinterpret_cast<const uint4 *>(b_row + k * BN);
+            };
+            uint32_t se = kSignExp;
+            asm volatile("" : "+v"(se));
+            rd(0, 0);
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    exact_row(acc[i], __uint_as_float(av[i]), bv, mm[i]);
+            for (int k = 0; k < BK; ++k) {
+                const int cur = k & 1;
+                if (k + 1 < BK)
+                    rd(k + 1, cur ^ 1);
+                __builtin_amdgcn_sched_barrier(0);
+                exact_step(acc, mm, al[cur], ah[cur], bq[cur], se);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         // Steps with an extreme b (every step in a dense workgroup): the
@@ -300,84 +345,105 @@ pam_exact_grad_kernel(GemmParams p) {
 #pragma unroll 1
         for (uint32_t todo = dense ? 0xFFFFu : slow; todo != 0u; todo &= todo - 1u) {
             const int kk = __builtin_ctz(todo);
-            uint32_t av[8], bv[8];
-            lds_frag<BK, LDA>(&sA, 0, kk, ty * 4, HM, av);
-            lds_frag<BK, LDB>(sB, 1, kk, tx * 4, HN, bv);
+            int rs = ty * 4, cs = c0;   // nothing of this rare path is kept across the chunks
+            asm volatile("" : "+v"(rs), "+v"(cs));
+            const uint4 al = *reinterpret_cast<const uint4 *>(sA + kk * BM + rs);
+            const uint4 ah = *reinterpret_cast<const uint4 *>(sA + kk * BM + HM + rs);
+            const uint4 bq = *reinterpret_cast<const uint4 *>(sBx + kk * BN + cs);
+            const uint32_t av[8] = {al.x, al.y, al.z, al.w, ah.x, ah.y, ah.z, ah.w};
+            const uint32_t bv[4] = {bq.x, bq.y, bq.z, bq.w};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < 4; ++j) {
                 if (dense || extreme(bv[j])) {
-                    const int h = j / 4;
-                    const int sh = 8 * (j % 4);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const int lr = i < 4 ? ty * 4 + i : HM + ty * 4 + (i - 4);
-                        const uint32_t f = (sE[lr][(h == 0 ? tx : HN / 4 + tx)] >> sh) & 0xFFu;
-                        general_fma(acc[i][j], __uint_as_float(av[i]), bv[j], (f << 23) | mm[i][j]);
+                        uint32_t mod = mm[i][j];
+                        const int row = m0 + (i < 4 ? rs + i : HM + rs + i - 4), col = n0 + cs + j;
+                        if (!dense && row < p.m && col < p.n)
+                            mod = __float_as_uint(p.Mod[(int64_t)row * p.ldm + col]);
+                        general_fma(acc[i][j], __uint_as_float(av[i]), bv[j], mod);
                     }
                 }
             }
         }
         // Outputs with an extreme Mod, every step.
-        if (!dense) {
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                if (side_on[e]) {
-                    const int lr = (int)(side_rc[e] >> 16);
-                    const int lc = (int)(side_rc[e] & 0xFFFFu);
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t idx = (uint32_t)e * NT + slot;
+            if (idx < nside) {
+                const int lr = (int)(sList[0][idx] >> 16);
+                const int lc = (int)(sList[0][idx] & 0xFFFFu);
+                const uint32_t mod = sList[1][idx];
 #pragma unroll 4
-                    for (int kk = 0; kk < BK; ++kk)
-                        general_fma(side_acc[e], __uint_as_float(sA[kk][lr]), sB[1][kk][lc], side_mod[e]);
-                }
+                for (int kk = 0; kk < BK; ++kk)
+                    general_fma(side_acc[e], __uint_as_float(sA[kk * BM + lr]), sBx[kk * BN + lc], mod);
             }
         }
     }
 
+    // The output tile in C, or this K slice's partial tile (packed, written
+    // whole).
     float *out;
     int64_t ld;
-    if (p.W != nullptr) {
-        out = p.W + (int64_t)split * p.m * p.n;
-        ld = p.n;
-    } else {
-        out = p.C;
+    int lim_m, lim_n;
+    bool vec;
+    if (whole) {
+        out = p.C + (int64_t)m0 * p.ldc + n0;
         ld = p.ldc;
+        lim_m = p.m - m0;
+        lim_n = p.n - n0;
+        vec = p.vec_c != 0;
+    } else {
+        out = p.W + ((int64_t)split * p.split_tiles + st) * (BM * BN);
+        ld = BN;
+        lim_m = BM;
+        lim_n = BN;
+        vec = true;
     }
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int row = m0 + (i < 4 ? ty * 4 + i : HM + ty * 4 + (i - 4));
-        if (row >= p.m)
+        int rs = ty * 4;   // rows are worked out one by one, not held for all
+        asm volatile("" : "+v"(rs));
+        const int lr = i < 4 ? rs + i : HM + rs + i - 4;
+        if (lr >= lim_m)
             continue;
-        float *orow = out + (int64_t)row * ld;
-        const float *mrow = p.Mod + (int64_t)row * p.ldm;
+        float *orow = out + (int64_t)lr * ld;
+        f32x4 v = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
+        if ((zero_mod >> (4 * i)) & 15u) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int col = n0 + (j < 4 ? tx * 4 + j : HN + tx * 4 + (j - 4));
-            if (col < p.n) {
-                const uint32_t mu = __float_as_uint(mrow[col]);
-                const bool zero_mod = (mu & kExpMask) == 0u;
-                // extreme-Mod outputs are written by the owner of their list entry
-                if (dense || !extreme(mu))
-                    orow[col] = zero_mod ? 0.0f : acc[i][j];
-            }
+            for (int j = 0; j < 4; ++j)
+                v[j] = (zero_mod >> (4 * i + j)) & 1u ? 0.0f : v[j];
+        }
+        // extreme-Mod outputs are written by the owner of their list entry
+        const uint32_t listed = dense ? 0u : (extreme_mod >> (4 * i)) & 15u;
+        if (vec && listed == 0u && c0 + 3 < lim_n) {
+            if (whole)
+                __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(orow + c0));
+            else
+                *reinterpret_cast<f32x4 *>(orow + c0) = v;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (c0 + j < lim_n && !((listed >> j) & 1u))
+                    orow[c0 + j] = v[j];
         }
     }
-    if (!dense) {
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            if (side_on[e]) {
-                const int row = m0 + (int)(side_rc[e] >> 16);
-                const int col = n0 + (int)(side_rc[e] & 0xFFFFu);
-                if (row < p.m && col < p.n)
-                    out[(int64_t)row * ld + col] = side_acc[e];
-            }
-        }
+    for (int e = 0; e < 2; ++e) {
+        const uint32_t idx = (uint32_t)e * NT + slot;
+        if (idx < nside)   // listed outputs lie inside the output
+            out[(int64_t)(sList[0][idx] >> 16) * ld + (sList[0][idx] & 0xFFFFu)] = side_acc[e];
     }
 }
 
 }  // namespace
 
 hipError_t launch_pam_exact_grad(bool trans_a, const GemmParams &p, hipStream_t stream) {
-    const int64_t tiles_m = (p.m + 127) / 128;
-    const dim3 grid((unsigned)(tiles_m * p.tiles_n), (unsigned)p.splits, 1);
+    const int64_t items = (int64_t)p.whole + (int64_t)p.split_tiles * p.splits;
+    if (items <= 0 || items > kMaxLaunchItems)
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)items);
     if (trans_a)
         hipLaunchKernelGGL(pam_exact_grad_kernel<true>, grid, dim3(256), 0, stream, p);
     else

@@ -72,40 +72,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pam_dma_tile.h"
 #include "pam_internal.h"
 #include "pam_scalar.h"
 
 namespace pamk {
-
-// One 16-byte copy per lane from global memory into LDS: lane i's bytes at
-// base + off land at LDS byte address lds_base + IMM + 16 i (the block
-// address in M0, the same for the whole wave).  Issued from inline asm, so
-// that the compiler does not make later LDS reads of other buffers wait for
-// the copy (it cannot tell the landing buffer from the compute buffers of
-// the same array); every read of the landing buffer is preceded by an
-// explicit wait for the vector-memory counter.  The kernels' compiled code uses M0 for nothing else (no other
-// LDS copies, no indexed register moves), so setting it here disturbs no
-// value the compiler keeps there.
-template <int IMM>
-__device__ __forceinline__ void dma_copy16(const char *base, uint32_t off, uint32_t lds_base) {
-    // base and lds_base are the same for the whole wave; reading them from
-    // the first lane puts them in scalar registers, as the instruction
-    // requires.
-    const uint2 b = __builtin_bit_cast(uint2, base);
-    const uint64_t sb = __builtin_bit_cast(
-        uint64_t, make_uint2(__builtin_amdgcn_readfirstlane(b.x), __builtin_amdgcn_readfirstlane(b.y)));
-    const uint32_t lb = __builtin_amdgcn_readfirstlane(lds_base);
-    // One wait state between the scalar write of M0 and the copy that reads
-    // it (the LDS-DMA read-after-SALU-write hazard of this generation).
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(off), "s"(sb), "s"(lb), "i"(IMM)
-                 : "memory", "m0", "scc");
-}
-
-// LDS byte address of an element of a __shared__ array: the low 32 bits of
-// its generic address (no null-pointer test as in a cast to the LDS space).
-__device__ __forceinline__ uint32_t lds_addr(const uint32_t *p) { return (uint32_t)(uintptr_t)p; }
 
 // One micro-tile row of an S2 or S3 step from A's own encoding a: first
 // 1 + M_A (exponent field 127, a's mantissa) and +-2^E_A (a with its mantissa
@@ -192,327 +163,6 @@ __device__ __forceinline__ void dma_frag(const uint32_t *p, int half, uint32_t (
     out[0] = lo.x; out[1] = lo.y; out[2] = lo.z; out[3] = lo.w;
     out[4] = hi.x; out[5] = hi.y; out[6] = hi.z; out[7] = hi.w;
 }
-
-// One operand's D x BK chunk (D = rows of op(A) or columns of op(B)) in
-// segments of four elements consecutive in memory; T is the operand's
-// element type (float or bfloat16 bits).
-//
-// KCONTIG: a segment is (row o, k quad).  Thread t stages the L rows
-// j * L .. j * L + L - 1 of one k quad kq, so that it can write each k of them
-// as one L-word LDS store.  Lane 16 * q + i of a wave takes row group
-// j = 16 * (wave / (BK / 16)) + i and k quad kq = q + 4 * (wave % (BK / 16)):
-// with float32 operands, one copy instruction reads 16 rows x 64 contiguous
-// bytes (16 cache lines), and the 16 lanes of each store pass write 16
-// consecutive row groups of one k row (no bank conflicts).
-//
-// Otherwise a segment is (k, column quad); thread t's segment r is number
-// t + r * NT, so consecutive lanes hold consecutive column quads of one k.
-template <int D, int BK, int NT, bool KCONTIG, typename T>
-struct DmaTile {
-    static constexpr int SEGS = D * BK / 4;
-    static constexpr int L = SEGS / NT;                  // segments per thread
-    static constexpr int G = D / L;                      // KCONTIG: row groups
-    static constexpr int KS = BK / 16;                   // KCONTIG: waves per 16 row groups
-    static constexpr int NW = NT / 64;
-    static constexpr bool kWide = sizeof(T) == 4;        // float32 operands; else bfloat16
-    static constexpr int EPC = 16 / (int)sizeof(T);      // elements per 16-byte copy
-    static constexpr int CL = D * BK / EPC / NT;         // copies per thread
-    static_assert(L * NT == SEGS && (L == 2 || L == 4), "chunk does not divide over the threads");
-    static_assert(CL * EPC * NT == D * BK && CL >= 1, "chunk copies do not divide over the threads");
-    static_assert(!KCONTIG || (G % 16 == 0 && BK % 16 == 0 && (G / 16) * KS == NW), "bad K-contiguous segment split");
-
-    uint4 v[L];          // the segments being encoded (live only at the chunk boundary)
-
-    static __device__ __forceinline__ int seg_o(int t, int r) {
-        return KCONTIG ? (16 * ((t >> 6) / KS) + (t & 15)) * L + r : ((t + r * NT) % (D / 4)) * 4;
-    }
-    static __device__ __forceinline__ int seg_k(int t, int r) {
-        return KCONTIG ? (((t & 63) >> 4) + 4 * ((t >> 6) % KS)) * 4 : (t + r * NT) / (D / 4);
-    }
-
-    // Copies.  A float32 copy is one segment (seg_o / seg_k).  A bfloat16
-    // copy is eight elements consecutive in memory, and a wave copies exactly
-    // the elements its own lanes stage (so that, after its own wait for the
-    // copies, it reads no other wave's): copy r of lane i takes q = i + 64 r
-    // of the wave's pieces.  K-contiguous: the wave stages 16 L rows x 16 k
-    // (row groups 16 (w / KS) + 0..15, k quads 4 (w % KS) + 0..3), piece q is
-    // row q / 2 of them, k octet q % 2.  Otherwise the wave's segments r' =
-    // 0..L-1 are 64 consecutive column quads each (from quad 64 w + r' NT of
-    // the k-major order), piece q is octet q % 32 of run q / 32.  Either way
-    // consecutive lanes read consecutive 16-byte pieces of the operand.
-    static __device__ __forceinline__ int copy_o(int t, int r) {
-        if constexpr (kWide)
-            return seg_o(t, r);
-        const int q = (t & 63) + 64 * r;
-        if (KCONTIG)
-            return 16 * L * ((t >> 6) / KS) + q / 2;
-        return (((64 * (t >> 6) + (q / 32) * NT) / 2 + q % 32) % (D / 8)) * 8;
-    }
-    static __device__ __forceinline__ int copy_k(int t, int r) {
-        if constexpr (kWide)
-            return seg_k(t, r);
-        const int q = (t & 63) + 64 * r;
-        if (KCONTIG)
-            return 16 * ((t >> 6) % KS) + 8 * (q & 1);
-        return ((64 * (t >> 6) + (q / 32) * NT) / 2 + q % 32) / (D / 8);
-    }
-
-    // Byte offset of copy r from its chunk's base.  Rows past o_lim are
-    // clamped to the last valid row (their outputs are discarded); a copy
-    // straddling the last valid column is not made (copyable) and its
-    // segments are loaded element by element.  In builds for three or four
-    // waves per SIMD recomputed per chunk from the thread index, so that no
-    // per-thread offsets stay live across the K loop.  The leading dimension
-    // is below 2^22 elements (the library rejects larger ones), so its bytes
-    // and the row or k index fit a 24-bit multiply.
-    static __device__ __forceinline__ uint32_t boff(int tid, int r, int64_t ld, int o0, int o_lim) {
-        const int o = copy_o(tid, r);
-        const int kk = copy_k(tid, r);
-        const uint32_t es = (uint32_t)sizeof(T);
-        const uint32_t ldb = (uint32_t)ld * es;
-        if (KCONTIG)
-            return __umul24((uint32_t)min(o, o_lim - 1 - o0), ldb) + (uint32_t)kk * es;
-        return __umul24((uint32_t)kk, ldb) + (uint32_t)o * es;
-    }
-    static __device__ __forceinline__ bool copyable(int tid, int r, int o0, int o_lim) {
-        return KCONTIG || o0 + copy_o(tid, r) + EPC - 1 < o_lim;
-    }
-    // Every copy of the tile is made (the same for the whole workgroup): the
-    // tile lies inside the operand, or it is K-contiguous.
-    static __device__ __forceinline__ bool all_copyable(int o0, int o_lim) { return KCONTIG || o0 + D <= o_lim; }
-
-    // Start copying the chunk at `base` into the landing buffer at byte
-    // RAW_OFF of the LDS array; lds_w is the LDS byte address of that array
-    // plus 1024 per wave index, so that copy r of wave w lands in block
-    // (r * NW + w) at lds_w + RAW_OFF + r * NW * 1024 (16 bytes per lane).
-    // Called only for an interior chunk of an aligned operand.
-    template <int RAW_OFF, int R>
-    static __device__ __forceinline__ void copy_seg(const char *cb, uint32_t lds_w, int tid, int64_t ld, int o0,
-                                                    int o_lim) {
-        dma_copy16<RAW_OFF + R * NW * 1024>(cb, boff(tid, R, ld, o0, o_lim), lds_w);
-    }
-    template <int RAW_OFF>
-    static __device__ __forceinline__ void copy(const T *__restrict__ base, uint32_t lds_w, int tid, int64_t ld,
-                                                int o0, int o_lim) {
-        const char *cb = reinterpret_cast<const char *>(base);
-        static_assert(CL == 1 || CL == 2 || CL == 4, "copies per thread");
-        if (all_copyable(o0, o_lim)) {
-            copy_seg<RAW_OFF, 0>(cb, lds_w, tid, ld, o0, o_lim);
-            if constexpr (CL >= 2)
-                copy_seg<RAW_OFF, 1>(cb, lds_w, tid, ld, o0, o_lim);
-            if constexpr (CL == 4) {
-                copy_seg<RAW_OFF, 2>(cb, lds_w, tid, ld, o0, o_lim);
-                copy_seg<RAW_OFF, 3>(cb, lds_w, tid, ld, o0, o_lim);
-            }
-            return;
-        }
-        if (copyable(tid, 0, o0, o_lim))
-            copy_seg<RAW_OFF, 0>(cb, lds_w, tid, ld, o0, o_lim);
-        if constexpr (CL >= 2) {
-            if (copyable(tid, 1, o0, o_lim))
-                copy_seg<RAW_OFF, 1>(cb, lds_w, tid, ld, o0, o_lim);
-        }
-        if constexpr (CL == 4) {
-            if (copyable(tid, 2, o0, o_lim))
-                copy_seg<RAW_OFF, 2>(cb, lds_w, tid, ld, o0, o_lim);
-            if (copyable(tid, 3, o0, o_lim))
-                copy_seg<RAW_OFF, 3>(cb, lds_w, tid, ld, o0, o_lim);
-        }
-    }
-
-    // Where segment r of this thread (wave w, lane) sits in the landing
-    // buffer: the word offset of its 16 (float32) or 8 (bfloat16) bytes.  A
-    // float32 segment is the lane's own copy r (block r * NW + w); a bfloat16
-    // segment is half of the copy of its eight elements, made by a lane of
-    // the same wave.
-    static __device__ __forceinline__ uint32_t slot_of(int w, int lane, int r) {
-        if constexpr (kWide)
-            return (uint32_t)((r * NW + w) * 256 + lane * 4);
-        const int q = KCONTIG ? ((lane & 15) * L + r) * 2 + (lane >> 5) : r * 32 + lane / 2;
-        const int half = KCONTIG ? (lane >> 4) & 1 : lane & 1;
-        return (uint32_t)(((q / 64) * NW + w) * 256 + (q % 64) * 4 + half * 2);
-    }
-    // Whether the copy holding segment r was made (see copyable).
-    static __device__ __forceinline__ bool seg_copied(int tid, int r, int o0, int o_lim) {
-        if constexpr (kWide)
-            return copyable(tid, r, o0, o_lim);
-        return KCONTIG || o0 + (seg_o(tid, r) & ~7) + 7 < o_lim;
-    }
-    // Reads through an LDS-space pointer: the compiler then cannot merge a
-    // landing-buffer read with the element-by-element global loads of the
-    // other branch into one generic (flat) load.
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
-    typedef __attribute__((address_space(3))) const u32x2 lds_u32x2;
-    static __device__ __forceinline__ uint4 read_slot(const uint32_t *raw, uint32_t off) {
-        if constexpr (kWide) {
-            const u32x4 x = *(lds_u32x4 *)(raw + off);
-            return make_uint4(x[0], x[1], x[2], x[3]);
-        }
-        const u32x2 y = *(lds_u32x2 *)(raw + off);
-        const uint2 d = make_uint2(y[0], y[1]);
-        // Four bfloat16 elements widened exactly to float32 encodings.
-        return make_uint4(d.x << 16, d.x & 0xFFFF0000u, d.y << 16, d.y & 0xFFFF0000u);
-    }
-
-    // The thread's segments of chunk [k0, k0 + BK): from the landing buffer
-    // when they were copied, else element by element from global memory
-    // (elements at k >= k_lim are zero).
-    __device__ __forceinline__ void fetch(const uint32_t *raw, int w, int lane, bool copied,
-                                          const T *__restrict__ base, int64_t ld, int o0, int o_lim, int k0,
-                                          int k_lim, int tid) {
-        if (copied && all_copyable(o0, o_lim)) {
-            // The common case, one branch for all segments: the reads issue
-            // back to back and are waited for once.
-#pragma unroll
-            for (int r = 0; r < L; ++r)
-                v[r] = read_slot(raw, slot_of(w, lane, r));
-            return;
-        }
-#pragma unroll
-        for (int r = 0; r < L; ++r) {
-            if (copied && seg_copied(tid, r, o0, o_lim))
-                v[r] = read_slot(raw, slot_of(w, lane, r));
-            else
-                v[r] = load_elements(base, r, ld, o0, o_lim, k0, k_lim, tid);
-        }
-    }
-
-    static __device__ __forceinline__ uint32_t widen(float x) { return __float_as_uint(x); }
-    static __device__ __forceinline__ uint32_t widen(uint16_t h) { return (uint32_t)h << 16; }
-
-    static __device__ __forceinline__ uint4 load_elements(const T *base, int r, int64_t ld, int o0, int o_lim, int k0,
-                                                          int k_lim, int tid) {
-        const int o = seg_o(tid, r);
-        const int kk = seg_k(tid, r);
-        uint32_t e[4];
-        if (KCONTIG) {
-            // (a float32 segment is its own copy: boff is its offset)
-            const T *src = kWide ? reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
-                                                               boff(tid, r, ld, o0, o_lim))
-                                 : base + (int64_t)(min(o0 + o, o_lim - 1) - o0) * ld + kk;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                e[c] = (k0 + kk + c < k_lim) ? widen(src[c]) : 0u;
-        } else {
-            const T *row = kWide ? reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
-                                                               boff(tid, r, ld, o0, o_lim)) - o
-                                 : base + (int64_t)kk * ld;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                e[c] = (k0 + kk < k_lim) ? widen(row[min(o0 + o + c, o_lim - 1) - o0]) : 0u;
-        }
-        return make_uint4(e[0], e[1], e[2], e[3]);
-    }
-
-    // Round every held element to 23 - drop mantissa bits, nearest even (inf
-    // and NaN unchanged).
-    __device__ __forceinline__ void round_mantissa(int drop) {
-        const uint32_t low = (1u << drop) - 1u;
-        const uint32_t half_m1 = low >> 1;
-#pragma unroll
-        for (int r = 0; r < L; ++r) {
-            uint32_t e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t u = e[c];
-                const uint32_t rounded = (u + half_m1 + ((u >> drop) & 1u)) & ~low;
-                e[c] = ((u & kExpMask) == kExpMask) ? u : rounded;
-            }
-            v[r] = make_uint4(e[0], e[1], e[2], e[3]);
-        }
-    }
-
-    // One pass over the held elements with the exponent field moved to the
-    // top byte and the sign dropped (x << 1): per segment r the least such
-    // value (below 64 << 24 iff the segment holds an element below the S1
-    // range: a zero, denormal or |x| < 2^-63), and the largest over all
-    // elements, returned (at least 191 << 24 iff one needs the SPECIAL
-    // path: |x| >= 2^64, inf, NaN).
-    __device__ __forceinline__ uint32_t scan(uint32_t (&smin)[L]) const {
-        uint32_t mx = 0;
-#pragma unroll
-        for (int r = 0; r < L; ++r) {
-            const uint32_t j0 = v[r].x << 1, j1 = v[r].y << 1, j2 = v[r].z << 1, j3 = v[r].w << 1;
-            smin[r] = min(min(j0, j1), min(j2, j3));
-            mx = max(mx, max(max(j0, j1), max(j2, j3)));
-        }
-        return mx;
-    }
-    static __device__ __forceinline__ bool low_seg(uint32_t smin) { return smin < (64u << 24); }
-
-    // A denormal element to its signed zero (multiplying by 1.0 flushes it;
-    // NaN stays NaN).  Needed for B only, and only where scan() found an
-    // element below the S1 range.
-    __device__ __forceinline__ void flush_denormals() {
-#pragma unroll
-        for (int r = 0; r < L; ++r) {
-            uint32_t e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                asm("v_mul_f32 %0, 1.0, %1" : "=v"(e[c]) : "v"(e[c]));
-            v[r] = make_uint4(e[0], e[1], e[2], e[3]);
-        }
-    }
-
-    // Element encodings: A as it is; B as b' = b - bias (denormals already
-    // flushed).
-    static __device__ __forceinline__ uint32_t enc(uint32_t u, bool is_b) { return is_b ? u - kBias : u; }
-
-    // Write the encoded chunk k-major into s[k * D + o] and mark the step
-    // masks: bit k % KPG of the word of k-group k / KPG.
-    template <int KPG, typename SlotOf>
-    __device__ __forceinline__ void store(uint32_t *s, bool is_b, int tid, const uint32_t (&smin)[L], uint32_t *mask,
-                                          int slots, SlotOf slot_of) const {
-        if (KCONTIG) {
-            // One address; the four k rows at constant offsets from it.
-            uint32_t *const row0 = s + seg_k(tid, 0) * D + seg_o(tid, 0);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                uint32_t w[L];
-#pragma unroll
-                for (int r = 0; r < L; ++r) {
-                    const uint32_t u = c == 0 ? v[r].x : c == 1 ? v[r].y : c == 2 ? v[r].z : v[r].w;
-                    w[r] = enc(u, is_b);
-                }
-                uint32_t *dst = row0 + c * D;
-                if constexpr (L == 2)
-                    *reinterpret_cast<uint2 *>(dst) = make_uint2(w[0], w[1]);
-                else
-                    *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < L; ++r) {
-                const int o = seg_o(tid, r);
-                const int kk = seg_k(tid, r);
-                *reinterpret_cast<uint4 *>(s + kk * D + o) =
-                    make_uint4(enc(v[r].x, is_b), enc(v[r].y, is_b), enc(v[r].z, is_b), enc(v[r].w, is_b));
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < L; ++r) {
-            // Rare: the wave skips this unless one of its lanes holds such an
-            // element in segment r.
-            if (low_seg(smin[r])) {
-                const uint32_t e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-                const int o = seg_o(tid, r);
-                const int kk = seg_k(tid, r);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t ex = e[c] & kExpMask;
-                    if (ex < (64u << 23)) {
-                        const int k = KCONTIG ? kk + c : kk;
-                        const uint32_t bit = 1u << (k % KPG);
-                        atomicOr(&mask[(k / KPG) * slots + slot_of(KCONTIG ? o : o + c)],
-                                 ex != 0u ? (bit | (bit << 16)) : bit);
-                    }
-                }
-            }
-        }
-    }
-};
 
 // Waves per SIMD the tile is compiled for (registers per wave 512 / waves),
 // matching what its LDS footprint allows on a 160 KB compute unit.

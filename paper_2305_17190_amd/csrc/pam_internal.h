@@ -41,6 +41,7 @@ struct GemmParams {
     // mantissas set each term's carry (row-major, leading dimension ldm).
     const float *Mod;
     int64_t ldm;
+    int32_t vec_mod;      // float4 loads of Mod are aligned
 };
 
 hipError_t launch_pam_mul(const float *a, const float *b, float *out, int64_t n, hipStream_t stream);
@@ -66,8 +67,8 @@ hipError_t launch_pam_gemm(int tile_m, int tile_n, int kgroups, bool trans_a, bo
 hipError_t launch_pam_gemm_dma(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
                                const GemmParams &p, hipStream_t stream);
 
-// C of the split tiles of a matrix product launch: element by element the sum
-// over s = 0, 1, ... of W[s][t][.][.], in that order.
+// C of the split tiles of a product launch: element by element the sum over s
+// of W[s][t][.][.], in an order fixed by the number of slices.
 hipError_t launch_split_tile_reduce(int tile_m, int tile_n, const GemmParams &p, hipStream_t stream);
 
 // Bytes of the static split-K scratch pam_gemm_batched_noalloc uses, and its
@@ -75,18 +76,15 @@ hipError_t launch_split_tile_reduce(int tile_m, int tile_n, const GemmParams &p,
 constexpr size_t kScratchBytes = (size_t)64 << 20;
 hipError_t scratch_address(void **out);
 
-// Workgroups one matrix product launch may hold (its grid, in threads, stays
+// Workgroups one product launch may hold (its grid, in threads, stays
 // below 2^32).
 constexpr int64_t kMaxLaunchItems = 16777215;
 
 // Exact-derivative product (pam_exact_grad.hip): C(r, c) = sum_q op(A)(r, q)
-// d(Mod(r, c) .^ B(q, c)) / dMod(r, c); 128 x 128 tiles, grid (tiles, splits).
+// d(Mod(r, c) .^ B(q, c)) / dMod(r, c); tiles of kExactTileM x kExactTileN,
+// work items and partial sums as in a matrix product launch.
+constexpr int kExactTileM = 128, kExactTileN = 64;
 hipError_t launch_pam_exact_grad(bool trans_a, const GemmParams &p, hipStream_t stream);
-
-// Exact-derivative products: C[b][i][j] = sum_s W[b][s][i][j], s in
-// increasing order.
-hipError_t launch_splitk_reduce(const float *W, float *C, int32_t m, int32_t n, int64_t ldc,
-                                int64_t strideC, int32_t splits, int64_t batch, hipStream_t stream);
 
 // C[b][i][j] = +0.0f for a k == 0 product.
 hipError_t launch_fill_zero(float *C, int32_t m, int32_t n, int64_t ldc, int64_t strideC,

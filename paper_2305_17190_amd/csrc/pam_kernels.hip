@@ -42,27 +42,8 @@ __device__ __forceinline__ void store_out4(float *p, float a, float b, float c, 
         *reinterpret_cast<f32x4 *>(p) = v;
 }
 
-__global__ void __launch_bounds__(256) splitk_reduce_kernel(const float *__restrict__ W, float *__restrict__ C,
-                                                            int32_t m, int32_t n, int64_t ldc, int64_t strideC,
-                                                            int32_t splits, int64_t total) {
-    const int64_t mn = (int64_t)m * n;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += stride) {
-        const int64_t b = idx / mn;
-        const int64_t r = idx - b * mn;
-        const int64_t i = r / n;
-        const int64_t j = r - i * n;
-        const float *w = W + b * splits * mn + r;
-        float s = 0.0f;
-        for (int q = 0; q < splits; ++q)
-            s += w[q * mn];
-        C[b * strideC + i * ldc + j] = s;
-    }
-}
-
 // Each workgroup adds the K slices of a 256 x 4-output part of one split
-// tile (grid-stride over the parts); each thread four consecutive outputs,
-// slice by slice.
+// tile (grid-stride over the parts); each thread four consecutive outputs.
 __global__ void __launch_bounds__(256) split_tile_reduce_kernel(GemmParams p, int bm, int bn) {
     const int gpr = bn / 4;                      // four-output groups per tile row
     const int parts = bm * bn / 4 / 256;         // parts per tile
@@ -83,8 +64,9 @@ __global__ void __launch_bounds__(256) split_tile_reduce_kernel(GemmParams p, in
             continue;
         const float *w = p.W + t * tile_elems + r * bn + c;
         float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        // Eight slices' loads in flight before their adds (in slice order):
-        // a thread's loads are independent, only the sum is sequential.
+        // Eight slices' loads in flight before their adds.  The eight are added
+        // in pairs, then the pairs: the same order on every call, and shorter
+        // chains of roundings than one running sum.
         typedef float f32x4 __attribute__((ext_vector_type(4)));
         int q = 0;
         for (; q + 8 <= p.splits; q += 8) {
@@ -92,13 +74,11 @@ __global__ void __launch_bounds__(256) split_tile_reduce_kernel(GemmParams p, in
 #pragma unroll
             for (int u = 0; u < 8; ++u)
                 x[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(w + (q + u) * slice));
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                sum.x += x[u].x;
-                sum.y += x[u].y;
-                sum.z += x[u].z;
-                sum.w += x[u].w;
-            }
+            const f32x4 y = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+            sum.x += y.x;
+            sum.y += y.y;
+            sum.z += y.z;
+            sum.w += y.w;
         }
         for (; q < p.splits; ++q) {
             const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(w + q * slice));
@@ -125,17 +105,6 @@ hipError_t launch_split_tile_reduce(int tile_m, int tile_n, const GemmParams &p,
     const int64_t parts = (int64_t)p.split_tiles * (tile_m * tile_n / 4 / 256);
     const int64_t blocks = std::min<int64_t>(parts, 256 * 32);
     hipLaunchKernelGGL(split_tile_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p, tile_m, tile_n);
-    return hipGetLastError();
-}
-
-hipError_t launch_splitk_reduce(const float *W, float *C, int32_t m, int32_t n, int64_t ldc, int64_t strideC,
-                                int32_t splits, int64_t batch, hipStream_t stream) {
-    const int64_t total = batch * (int64_t)m * n;
-    if (total <= 0)
-        return hipSuccess;
-    const int64_t blocks = std::min<int64_t>((total + 255) / 256, 256 * 32);
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, W, C, m, n, ldc, strideC,
-                       splits, total);
     return hipGetLastError();
 }
 

@@ -184,3 +184,34 @@ def test_workload5_exact_dx_sampled_rows():
     rows = np.random.default_rng(812).choice(x.shape[0], size=4, replace=False)
     dxo, sdx, _, _ = pam_ref.pam_exact_grads_ref(dy[rows], x[rows], w)
     check_gemm(dx.cpu().numpy()[rows], dxo, sdx, 4096, "w5 exact dX")
+
+
+@pytest.mark.parametrize("m,n,k,ta,pad", [(127, 63, 15, False, 0), (129, 65, 17, True, 0), (128, 64, 16, False, 4),
+                                          (257, 1, 33, True, 1), (1, 129, 700, False, 3), (140, 66, 2600, True, 0),
+                                          (130, 191, 1030, False, 1), (64, 64, 64, True, 0)])
+def test_tile_edges_and_views(m, n, k, ta, pad):
+    """Sizes around the 128 x 64 tile and its 16-step chunks, ragged and (pad
+    not a multiple of 4) unaligned rows of every operand and of the output,
+    long K in slices, with zero, tiny and huge values in B and Mod and a Mod
+    row of tiny values (more listed outputs in one tile than ordinary data
+    has)."""
+    import torch
+    note(f"exact grad tile edges m={m} n={n} k={k} ta={ta} pad={pad}")
+    g = np.random.default_rng(850 + m + n + k)
+
+    def padded(x):
+        full = np.full((x.shape[0], x.shape[1] + pad), np.nan, np.float32)
+        full[:, :x.shape[1]] = x
+        return to_dev(full)[:, :x.shape[1]]
+
+    a = small_dy((m, k), g)
+    b = g.standard_normal((k, n)).astype(np.float32)
+    mod = g.standard_normal((m, n)).astype(np.float32)
+    for x in (b, mod):
+        pick = g.random(x.shape) < 0.01
+        x[pick] = region_values(x.shape, g)[pick]
+    mod[m // 2] = region_values((n,), g, lo_share=1.0, hi_share=0.0, zero_share=0.0)
+    out = torch.full((m, n + pad), float("nan"), device=device())[:, :n]
+    pam.exact_grad(padded(np.ascontiguousarray(a.T) if ta else a), padded(b), padded(mod), trans_a=ta, out=out)
+    ref, s, _, _ = pam_ref.pam_exact_grads_ref(a, mod, np.ascontiguousarray(b))
+    check_gemm(out.cpu().numpy(), ref, s, k, "exact grad tile edges")
