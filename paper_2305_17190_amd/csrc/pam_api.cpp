@@ -29,8 +29,6 @@ pam_status_t fail_hip(hipError_t e, const char *what) {
     return PAM_ERROR_LAUNCH;
 }
 
-bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
 constexpr int64_t kMaxDim = 0x7FFFFFFF;
 constexpr int64_t kMaxSplits = 64;
 // 128 rows of a panel, in bytes, must fit the kernels' 32-bit offsets.
@@ -422,11 +420,6 @@ pam_status_t run_gemm(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t k,
     p.k = (int32_t)k;
     p.k_per_split = (int32_t)std::min<int64_t>(plan.k_per_split, kMaxDim);
     p.tiles_n = (int32_t)ceil_div(n, plan.tile_n);
-    // Operand copies of 16 bytes: four float32 or eight bfloat16 elements.
-    const int64_t per16 = bf16 ? 8 : 4;
-    p.vec_a = aligned16(A) && lda % per16 == 0 && (batch == 1 || sa % per16 == 0);
-    p.vec_b = aligned16(B) && ldb % per16 == 0 && (batch == 1 || sb % per16 == 0);
-    p.vec_c = aligned16(C) && ldc % 4 == 0 && (batch == 1 || sc % 4 == 0);
     p.round_drop = round_drop;
     p.tiles = (int32_t)L.tiles;
     p.splits = (int32_t)L.splits;
@@ -589,10 +582,6 @@ pam_status_t run_exact_grad(pam_op_t transA, int64_t m, int64_t n, int64_t k, co
     p.tiles_n = (int32_t)ceil_div(n, plan.tile_n);
     p.whole = (int32_t)(L.splits > 1 ? L.whole_tiles : L.tiles);
     p.split_tiles = (int32_t)(L.tiles - p.whole);
-    p.vec_a = aligned16(A) && lda % 4 == 0;
-    p.vec_b = aligned16(B) && ldb % 4 == 0;
-    p.vec_c = aligned16(C) && ldc % 4 == 0;
-    p.vec_mod = aligned16(Mod) && ldm % 4 == 0;
     p.C = C;
     p.W = L.ws_bytes > 0 ? static_cast<float *>(ext->ptr) : nullptr;
     hipError_t e = pamk::launch_pam_exact_grad(transA == PAM_OP_T, p, stream);

@@ -108,14 +108,13 @@ struct DmaTile {
         return ((64 * (t >> 6) + (q / 32) * NT) / 2 + q % 32) / (D / 8);
     }
 
-    // Byte offset of copy r from its chunk's base.  Rows past o_lim are
-    // clamped to the last valid row (their outputs are discarded); a copy
-    // straddling the last valid column is not made (copyable) and its
-    // segments are loaded element by element.  In builds for three or four
-    // waves per SIMD recomputed per chunk from the thread index, so that no
-    // per-thread offsets stay live across the K loop.  The leading dimension
-    // is below 2^22 elements (the library rejects larger ones), so its bytes
-    // and the row or k index fit a 24-bit multiply.
+    // Byte offset of copy r from its chunk's base, for a chunk and tile whose
+    // pieces all lie inside the operand (but for rows past o_lim, which are
+    // clamped to the last valid row: their outputs are discarded).  In builds
+    // for three or four waves per SIMD recomputed per chunk from the thread
+    // index, so that no per-thread offsets stay live across the K loop.  The
+    // leading dimension is below 2^22 elements (the library rejects larger
+    // ones), so its bytes and the row or k index fit a 24-bit multiply.
     static __device__ __forceinline__ uint32_t boff(int tid, int r, int64_t ld, int o0, int o_lim) {
         const int o = copy_o(tid, r);
         const int kk = copy_k(tid, r);
@@ -125,49 +124,81 @@ struct DmaTile {
             return __umul24((uint32_t)min(o, o_lim - 1 - o0), ldb) + (uint32_t)kk * es;
         return __umul24((uint32_t)kk, ldb) + (uint32_t)o * es;
     }
-    static __device__ __forceinline__ bool copyable(int tid, int r, int o0, int o_lim) {
-        return KCONTIG || o0 + copy_o(tid, r) + EPC - 1 < o_lim;
+    // What a tile's copies have to heed, the same for the whole workgroup:
+    // kEdge when it reaches past the last column of an operand that is not
+    // K-contiguous, kShort when a row of the operand (up to k = ke, or its
+    // o_lim columns) is shorter than a piece.
+    static constexpr uint32_t kEdge = 1u, kShort = 2u;
+    static __device__ __forceinline__ uint32_t kind(int ke, int o0, int o_lim) {
+        return (KCONTIG || o0 + D <= o_lim ? 0u : kEdge) | ((KCONTIG ? ke : o_lim) >= EPC ? 0u : kShort);
     }
-    // Every copy of the tile is made (the same for the whole workgroup): the
-    // tile lies inside the operand, or it is K-contiguous.
-    static __device__ __forceinline__ bool all_copyable(int o0, int o_lim) { return KCONTIG || o0 + D <= o_lim; }
+
+    // At the last k steps of a row, or at the last columns, a piece that
+    // would pass the end starts earlier, on the last EPC elements: every
+    // piece is copied whole and inside the operand, and fetch() picks a
+    // segment's elements out of it.  k_rem: valid k steps from the chunk's
+    // base.  First element (k or column, relative to the chunk's base) of the
+    // piece that would start at x; below zero by at most EPC - 1.
+    static __device__ __forceinline__ int piece_k(int kk, int k_rem) { return min(kk, k_rem - EPC); }
+    static __device__ __forceinline__ int piece_o(int o, int o0, int o_lim) { return min(o, o_lim - EPC - o0); }
+    // As boff, from EPC elements before the chunk's base.
+    static __device__ __forceinline__ uint32_t boff_edge(int tid, int r, int64_t ld, int o0, int o_lim, int k_rem) {
+        const int o = copy_o(tid, r);
+        const int kk = copy_k(tid, r);
+        const uint32_t es = (uint32_t)sizeof(T);
+        const uint32_t ldb = (uint32_t)ld * es;
+        if (KCONTIG)
+            return __umul24((uint32_t)min(o, o_lim - 1 - o0), ldb) + (uint32_t)(piece_k(kk, k_rem) + EPC) * es;
+        return __umul24((uint32_t)min(kk, k_rem - 1), ldb) + (uint32_t)(piece_o(o, o0, o_lim) + EPC) * es;
+    }
 
     // Start copying the chunk at `base` into the landing buffer at byte
     // RAW_OFF of the LDS array; lds_w is the LDS byte address of that array
     // plus 1024 per wave index, so that copy r of wave w lands in block
     // (r * NW + w) at lds_w + RAW_OFF + r * NW * 1024 (16 bytes per lane).
-    // Called only for an interior chunk of an aligned operand.
-    template <int RAW_OFF, int R>
-    static __device__ __forceinline__ void copy_seg(const char *cb, uint32_t lds_w, int tid, int64_t ld, int o0,
-                                                    int o_lim) {
-        dma_copy16<RAW_OFF + R * NW * 1024>(cb, boff(tid, R, ld, o0, o_lim), lds_w);
-    }
-    template <int RAW_OFF>
+    // Pieces may lie at any address: the copy needs no alignment of the
+    // operand.  k_rem >= 1.
+    // EDGE false: every chunk and tile of the launch lies inside the operand
+    // (but for rows past o_lim), and nothing of the edges is compiled in.
+    template <int RAW_OFF, bool EDGE>
     static __device__ __forceinline__ void copy(const T *__restrict__ base, uint32_t lds_w, int tid, int64_t ld,
-                                                int o0, int o_lim) {
+                                                int o0, int o_lim, int k_rem, uint32_t kind) {
         const char *cb = reinterpret_cast<const char *>(base);
         static_assert(CL == 1 || CL == 2 || CL == 4, "copies per thread");
-        if (all_copyable(o0, o_lim)) {
-            copy_seg<RAW_OFF, 0>(cb, lds_w, tid, ld, o0, o_lim);
+        if (!EDGE || (k_rem >= BK && kind == 0u)) {
+            dma_copy16<RAW_OFF>(cb, boff(tid, 0, ld, o0, o_lim), lds_w);
             if constexpr (CL >= 2)
-                copy_seg<RAW_OFF, 1>(cb, lds_w, tid, ld, o0, o_lim);
+                dma_copy16<RAW_OFF + NW * 1024>(cb, boff(tid, 1, ld, o0, o_lim), lds_w);
             if constexpr (CL == 4) {
-                copy_seg<RAW_OFF, 2>(cb, lds_w, tid, ld, o0, o_lim);
-                copy_seg<RAW_OFF, 3>(cb, lds_w, tid, ld, o0, o_lim);
+                dma_copy16<RAW_OFF + 2 * NW * 1024>(cb, boff(tid, 2, ld, o0, o_lim), lds_w);
+                dma_copy16<RAW_OFF + 3 * NW * 1024>(cb, boff(tid, 3, ld, o0, o_lim), lds_w);
             }
             return;
         }
-        if (copyable(tid, 0, o0, o_lim))
-            copy_seg<RAW_OFF, 0>(cb, lds_w, tid, ld, o0, o_lim);
-        if constexpr (CL >= 2) {
-            if (copyable(tid, 1, o0, o_lim))
-                copy_seg<RAW_OFF, 1>(cb, lds_w, tid, ld, o0, o_lim);
+        // Edges are rare: their addresses are worked out here, never kept.
+        asm volatile("" : "+v"(tid), "+s"(o0), "+s"(o_lim), "+s"(ld));
+        cb -= 16;
+        if (kind & kShort) {
+            // Rows shorter than a piece: its elements one by one, those
+            // before the row's first as zeros.
+            const int before = KCONTIG ? EPC - k_rem : EPC - (o_lim - o0);
+#pragma unroll 1
+            for (int r = 0; r < CL; ++r) {
+                const char *src = cb + boff_edge(tid, r, ld, o0, o_lim, k_rem);
+                const uint32_t dst = lds_w + RAW_OFF + (uint32_t)(r * NW) * 1024u + (uint32_t)(tid & 63) * 16u;
+#pragma unroll 1
+                for (int x = 0; x < EPC; ++x)
+                    *(lds_t *)(uintptr_t)(dst + (uint32_t)(x * (int)sizeof(T))) =
+                        x >= before ? *reinterpret_cast<const T *>(src + x * (int)sizeof(T)) : (T)0;
+            }
+            return;
         }
+        dma_copy16<RAW_OFF>(cb, boff_edge(tid, 0, ld, o0, o_lim, k_rem), lds_w);
+        if constexpr (CL >= 2)
+            dma_copy16<RAW_OFF + NW * 1024>(cb, boff_edge(tid, 1, ld, o0, o_lim, k_rem), lds_w);
         if constexpr (CL == 4) {
-            if (copyable(tid, 2, o0, o_lim))
-                copy_seg<RAW_OFF, 2>(cb, lds_w, tid, ld, o0, o_lim);
-            if (copyable(tid, 3, o0, o_lim))
-                copy_seg<RAW_OFF, 3>(cb, lds_w, tid, ld, o0, o_lim);
+            dma_copy16<RAW_OFF + 2 * NW * 1024>(cb, boff_edge(tid, 2, ld, o0, o_lim, k_rem), lds_w);
+            dma_copy16<RAW_OFF + 3 * NW * 1024>(cb, boff_edge(tid, 3, ld, o0, o_lim, k_rem), lds_w);
         }
     }
 
@@ -183,12 +214,6 @@ struct DmaTile {
         const int half = KCONTIG ? (lane >> 4) & 1 : lane & 1;
         return (uint32_t)(((q / 64) * NW + w) * 256 + (q % 64) * 4 + half * 2);
     }
-    // Whether the copy holding segment r was made (see copyable).
-    static __device__ __forceinline__ bool seg_copied(int tid, int r, int o0, int o_lim) {
-        if constexpr (kWide)
-            return copyable(tid, r, o0, o_lim);
-        return KCONTIG || o0 + (seg_o(tid, r) & ~7) + 7 < o_lim;
-    }
     // Reads through an LDS-space pointer: the compiler then cannot merge a
     // landing-buffer read with the element-by-element global loads of the
     // other branch into one generic (flat) load.
@@ -196,6 +221,7 @@ struct DmaTile {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
     typedef __attribute__((address_space(3))) const u32x2 lds_u32x2;
+    typedef __attribute__((address_space(3))) T lds_t;
     static __device__ __forceinline__ uint4 read_slot(const uint32_t *raw, uint32_t off) {
         if constexpr (kWide) {
             const u32x4 x = *(lds_u32x4 *)(raw + off);
@@ -207,55 +233,49 @@ struct DmaTile {
         return make_uint4(d.x << 16, d.x & 0xFFFF0000u, d.y << 16, d.y & 0xFFFF0000u);
     }
 
-    // The thread's segments of chunk [k0, k0 + BK): from the landing buffer
-    // when they were copied, else element by element from global memory
-    // (elements at k >= k_lim are zero).
-    __device__ __forceinline__ void fetch(const uint32_t *raw, int w, int lane, bool copied,
-                                          const T *__restrict__ base, int64_t ld, int o0, int o_lim, int k0,
-                                          int k_lim, int tid) {
-        if (copied && all_copyable(o0, o_lim)) {
+    // Element x of the piece that holds segment r.
+    static __device__ __forceinline__ uint32_t piece_element(const uint32_t *raw, int w, int lane, int r, int x) {
+        uint32_t slot = slot_of(w, lane, r);
+        if constexpr (!kWide)
+            slot = 2u * (slot & ~3u);   // the piece's first element
+        return widen(((const lds_t *)raw)[slot + (uint32_t)x]);
+    }
+
+    // The thread's segments of a chunk with k_rem valid k steps (the elements
+    // past them are zero; columns past o_lim repeat the last one, their
+    // outputs are discarded) from the landing buffer.
+    template <bool EDGE>
+    __device__ __forceinline__ void fetch(const uint32_t *raw, int w, int o0, int o_lim, int k_rem, uint32_t kind,
+                                          int tid) {
+        if (!EDGE || (k_rem >= BK && kind == 0u)) {
             // The common case, one branch for all segments: the reads issue
             // back to back and are waited for once.
 #pragma unroll
             for (int r = 0; r < L; ++r)
-                v[r] = read_slot(raw, slot_of(w, lane, r));
+                v[r] = read_slot(raw, slot_of(w, tid & 63, r));
             return;
         }
+        asm volatile("" : "+v"(tid), "+s"(o0), "+s"(o_lim), "+s"(w));   // as in copy()
 #pragma unroll
         for (int r = 0; r < L; ++r) {
-            if (copied && seg_copied(tid, r, o0, o_lim))
-                v[r] = read_slot(raw, slot_of(w, lane, r));
-            else
-                v[r] = load_elements(base, r, ld, o0, o_lim, k0, k_lim, tid);
+            const int o = seg_o(tid, r);
+            const int kk = seg_k(tid, r);
+            uint32_t e[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int k = KCONTIG ? kk + c : kk;
+                const int x = KCONTIG ? k - piece_k(kk & -EPC, k_rem)
+                                      : min(o + c, o_lim - 1 - o0) - piece_o(o & -EPC, o0, o_lim);
+                e[c] = 0u;
+                if (k < k_rem)
+                    e[c] = piece_element(raw, w, tid & 63, r, x);
+            }
+            v[r] = make_uint4(e[0], e[1], e[2], e[3]);
         }
     }
 
     static __device__ __forceinline__ uint32_t widen(float x) { return __float_as_uint(x); }
     static __device__ __forceinline__ uint32_t widen(uint16_t h) { return (uint32_t)h << 16; }
-
-    static __device__ __forceinline__ uint4 load_elements(const T *base, int r, int64_t ld, int o0, int o_lim, int k0,
-                                                          int k_lim, int tid) {
-        const int o = seg_o(tid, r);
-        const int kk = seg_k(tid, r);
-        uint32_t e[4];
-        if (KCONTIG) {
-            // (a float32 segment is its own copy: boff is its offset)
-            const T *src = kWide ? reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
-                                                               boff(tid, r, ld, o0, o_lim))
-                                 : base + (int64_t)(min(o0 + o, o_lim - 1) - o0) * ld + kk;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                e[c] = (k0 + kk + c < k_lim) ? widen(src[c]) : 0u;
-        } else {
-            const T *row = kWide ? reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
-                                                               boff(tid, r, ld, o0, o_lim)) - o
-                                 : base + (int64_t)kk * ld;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                e[c] = (k0 + kk < k_lim) ? widen(row[min(o0 + o + c, o_lim - 1) - o0]) : 0u;
-        }
-        return make_uint4(e[0], e[1], e[2], e[3]);
-    }
 
     // Round every held element to 23 - drop mantissa bits, nearest even (inf
     // and NaN unchanged).

@@ -125,10 +125,13 @@ __device__ __forceinline__ void exact_step(float (&acc)[8][4], const uint32_t (&
 #undef PAM_EXACT_ACC
 #undef PAM_EXACT_MOD
 
-// Four words of a row of Mod from column col (zero past n).
-__device__ __forceinline__ uint4 mod_quad(const float *row, int col, int n, bool vec) {
-    if (vec && col + 3 < n)
-        return *reinterpret_cast<const uint4 *>(row + col);
+// Four words of a row of Mod from column col (zero past n), at any address.
+__device__ __forceinline__ uint4 mod_quad(const float *row, int col, int n) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    if (col + 3 < n) {
+        const u32x4 x = *reinterpret_cast<const u32x4 *>(row + col);
+        return make_uint4(x[0], x[1], x[2], x[3]);
+    }
     uint32_t u[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -181,13 +184,13 @@ pam_exact_grad_kernel(GemmParams p) {
     const float *b_base = p.B + (int64_t)kb * p.ldb + n0;
     const int64_t a_step = TA ? (int64_t)BK * p.lda : BK;
     const int64_t b_step = (int64_t)BK * p.ldb;
-    const uint32_t flags = (p.vec_a != 0 ? 1u : 0u) | (p.vec_b != 0 ? 2u : 0u);
 
-    if (kb + BK <= ke) {
-        if (p.vec_a != 0)
-            TileA::template copy<0>(a_base, lds_w, tid, p.lda, m0, p.m);
-        if (p.vec_b != 0)
-            TileB::template copy<kRawA * 4>(b_base, lds_w, tid, p.ldb, n0, p.n);
+    // The copies' kinds (A's, then B's) as one scalar word, tested afresh in
+    // each chunk (conditions kept across the loop took lane masks, spilled).
+    const uint32_t kinds = TileA::kind(ke, m0, p.m) | TileB::kind(ke, n0, p.n) << 2;
+    if (nchunks > 0) {
+        TileA::template copy<0, true>(a_base, lds_w, tid, p.lda, m0, p.m, ke - kb, kinds & 3u);
+        TileB::template copy<kRawA * 4, true>(b_base, lds_w, tid, p.ldb, n0, p.n, ke - kb, kinds >> 2);
     }
     if (tid < 2)
         sSlow[tid] = 0u;
@@ -204,7 +207,7 @@ pam_exact_grad_kernel(GemmParams p) {
         const int lr = i < 4 ? ty * 4 + i : HM + ty * 4 + (i - 4);
         uint4 q = make_uint4(0u, 0u, 0u, 0u);
         if (m0 + lr < p.m)
-            q = mod_quad(p.Mod + (int64_t)(m0 + lr) * p.ldm, n0 + c0, p.n, p.vec_mod != 0);
+            q = mod_quad(p.Mod + (int64_t)(m0 + lr) * p.ldm, n0 + c0, p.n);
         mm[i][0] = q.x;
         mm[i][1] = q.y;
         mm[i][2] = q.z;
@@ -266,18 +269,17 @@ pam_exact_grad_kernel(GemmParams p) {
     TileA la;
     TileB lb;
     for (int c = 0; c < nchunks; ++c) {
-        const int k0 = kb + c * BK;
-        const bool interior = k0 + BK <= ke;
-        uint32_t fl = __builtin_amdgcn_readfirstlane(flags);
-        asm volatile("" : "+s"(fl));
+        const int k_rem = ke - kb - c * BK;   // k steps left, this chunk's included
+        uint32_t kd = __builtin_amdgcn_readfirstlane(kinds);
+        asm volatile("" : "+s"(kd));
         // Staging addresses are recomputed per chunk from the thread index
         // instead of staying in registers across the steps.
         int tid_c = tid;
         asm volatile("" : "+v"(tid_c));
         __builtin_amdgcn_s_setprio(1);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's copies of chunk c have landed
-        la.fetch(rawA, wave, tid_c & 63, interior && (fl & 1u), a_base + c * a_step, p.lda, m0, p.m, k0, ke, tid_c);
-        lb.fetch(rawB, wave, tid_c & 63, interior && (fl & 2u), b_base + c * b_step, p.ldb, n0, p.n, k0, ke, tid_c);
+        la.template fetch<true>(rawA, wave, m0, p.m, k_rem, kd & 3u, tid_c);
+        lb.template fetch<true>(rawB, wave, n0, p.n, k_rem, kd >> 2, tid_c);
         uint32_t smin[TileB::L];
         const uint32_t mx = lb.scan(smin);
         static_assert(TileB::L == 1, "one B segment per thread");
@@ -310,11 +312,9 @@ pam_exact_grad_kernel(GemmParams p) {
         if (tid == 0)
             sSlow[(c + 1) & 1] = 0u;   // next chunk's flags; last read one chunk ago
         // The next chunk's copies land while this one is computed.
-        if (c + 1 < nchunks && k0 + 2 * BK <= ke) {
-            if (fl & 1u)
-                TileA::template copy<0>(a_base + (c + 1) * a_step, lds_w, tid_c, p.lda, m0, p.m);
-            if (fl & 2u)
-                TileB::template copy<kRawA * 4>(b_base + (c + 1) * b_step, lds_w, tid_c, p.ldb, n0, p.n);
+        if (c + 1 < nchunks) {
+            TileA::template copy<0, true>(a_base + (c + 1) * a_step, lds_w, tid_c, p.lda, m0, p.m, k_rem - BK, kd & 3u);
+            TileB::template copy<kRawA * 4, true>(b_base + (c + 1) * b_step, lds_w, tid_c, p.ldb, n0, p.n, k_rem - BK, kd >> 2);
         }
         __builtin_amdgcn_s_setprio(0);
 
@@ -386,21 +386,18 @@ pam_exact_grad_kernel(GemmParams p) {
     float *out;
     int64_t ld;
     int lim_m, lim_n;
-    bool vec;
     if (whole) {
         out = p.C + (int64_t)m0 * p.ldc + n0;
         ld = p.ldc;
         lim_m = p.m - m0;
         lim_n = p.n - n0;
-        vec = p.vec_c != 0;
     } else {
         out = p.W + ((int64_t)split * p.split_tiles + st) * (BM * BN);
         ld = BN;
         lim_m = BM;
         lim_n = BN;
-        vec = true;
     }
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));   // stored at any address
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         int rs = ty * 4;   // rows are worked out one by one, not held for all
@@ -417,7 +414,7 @@ pam_exact_grad_kernel(GemmParams p) {
         }
         // extreme-Mod outputs are written by the owner of their list entry
         const uint32_t listed = dense ? 0u : (extreme_mod >> (4 * i)) & 15u;
-        if (vec && listed == 0u && c0 + 3 < lim_n) {
+        if (listed == 0u && c0 + 3 < lim_n) {
             if (whole)
                 __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(orow + c0));
             else

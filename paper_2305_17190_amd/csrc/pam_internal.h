@@ -33,15 +33,11 @@ struct GemmParams {
     int32_t tiles;        // matrix products: tiles per matrix
     int32_t whole;        // matrix products: whole-K work items
     int32_t split_tiles;  // matrix products: tiles split into `splits` K slices
-    int32_t vec_a;        // float4 global loads of A are aligned
-    int32_t vec_b;        // float4 global loads of B are aligned
-    int32_t vec_c;        // float4 stores of the output are aligned
     int32_t round_drop;   // 0, or 23 - m: round every input to m mantissa bits first
     // Exact-derivative products only: the output-shaped operand whose
     // mantissas set each term's carry (row-major, leading dimension ldm).
     const float *Mod;
     int64_t ldm;
-    int32_t vec_mod;      // float4 loads of Mod are aligned
 };
 
 hipError_t launch_pam_mul(const float *a, const float *b, float *out, int64_t n, hipStream_t stream);
@@ -61,9 +57,7 @@ hipError_t launch_pam_gemm(int tile_m, int tile_n, int kgroups, bool trans_a, bo
                            const GemmParams &p, hipStream_t stream);
 
 // The kernel behind launch_pam_gemm (pam_gemm_dma.hip): operand chunks
-// copied into LDS by the memory pipeline.  With bf16, the copies need the
-// operand 16-byte aligned with leading dimension and stride multiples of 8
-// elements (p.vec_a / p.vec_b), else its elements are loaded one by one.
+// copied into LDS by the memory pipeline.
 hipError_t launch_pam_gemm_dma(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
                                const GemmParams &p, hipStream_t stream);
 

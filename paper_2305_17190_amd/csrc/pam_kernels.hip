@@ -30,16 +30,12 @@ hipError_t launch_pam_gemm(int tile_m, int tile_n, int kgroups, bool trans_a, bo
 // Split-K reduction and k == 0 fill
 // ---------------------------------------------------------------------------
 
-// Four outputs to 16-byte aligned memory: the final C with the non-temporal
-// hint (written once), split partial sums without it (the reduce reads them
-// back soon, mostly from cache).
-__device__ __forceinline__ void store_out4(float *p, float a, float b, float c, float d, bool final_c) {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Four outputs of the final C, at any address, with the non-temporal hint
+// (written once).
+__device__ __forceinline__ void store_out4(float *p, float a, float b, float c, float d) {
+    typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
     const f32x4 v = {a, b, c, d};
-    if (final_c)
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
-    else
-        *reinterpret_cast<f32x4 *>(p) = v;
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(p));
 }
 
 // Each workgroup adds the K slices of a 256 x 4-output part of one split
@@ -88,8 +84,8 @@ __global__ void __launch_bounds__(256) split_tile_reduce_kernel(GemmParams p, in
             sum.w += x.w;
         }
         float *crow = p.C + bz * p.strideC + (int64_t)(m0 + r) * p.ldc + n0;
-        if (p.vec_c && n0 + c + 3 < p.n) {
-            store_out4(crow + c, sum.x, sum.y, sum.z, sum.w, true);
+        if (n0 + c + 3 < p.n) {
+            store_out4(crow + c, sum.x, sum.y, sum.z, sum.w);
         } else {
             const float sv[4] = {sum.x, sum.y, sum.z, sum.w};
             for (int j = 0; j < 4; ++j)
