@@ -361,32 +361,78 @@ struct DmaTile {
         }
     }
 
-    // Write the encoded chunk and mark the step masks: bit k % KPG of the
-    // word of k-group k / KPG.
+    // Mark the step masks: bit k % KPG of the word of k-group k / KPG and of the
+    // element's slot when it has exponent field below 64, also bit 16 +
+    // k % KPG when it is a normal number.  Eight consecutive lanes hold
+    // elements of one slot and of one k quad (K-contiguous) or k row: their
+    // words are combined before the LDS atomic.  (One atomic per element
+    // cost a chunk of ReLU activations, half of them zeros, as much as its
+    // compute steps: 32 lanes a time on one address.)
     template <int KPG, typename SlotOf>
-    __device__ __forceinline__ void store(uint32_t *s, bool is_b, int tid, const uint32_t (&smin)[L], uint32_t *mask,
-                                          int slots, SlotOf slot_of) const {
-        store_values(s, is_b, tid);
+    __device__ __forceinline__ void mark(int tid, const uint32_t (&smin)[L], uint32_t *mask, int slots,
+                                         SlotOf slot_of) const {
+        // Segments r of one k-group: all, or runs of RUN.
+        constexpr int STEP = KCONTIG ? 1 : NT * 4 / D;   // k rows from a thread's segment to its next
+        constexpr int RUN = KCONTIG || KPG / STEP >= L ? L : KPG / STEP;
+        static_assert(KPG % STEP == 0 && RUN >= 1 && L % RUN == 0, "segments do not divide over the k-groups");
 #pragma unroll
-        for (int r = 0; r < L; ++r) {
-            // Rare: the wave skips this unless one of its lanes holds such an
-            // element in segment r.
-            if (low_seg(smin[r])) {
-                const uint32_t e[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
-                const int o = seg_o(tid, r);
-                const int kk = seg_k(tid, r);
+        for (int r0 = 0; r0 < L; r0 += RUN) {
+            uint32_t least = smin[r0];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t ex = e[c] & kExpMask;
-                    if (ex < (64u << 23)) {
-                        const int k = KCONTIG ? kk + c : kk;
-                        const uint32_t bit = 1u << (k % KPG);
-                        atomicOr(&mask[(k / KPG) * slots + slot_of(KCONTIG ? o : o + c)],
-                                 ex != 0u ? (bit | (bit << 16)) : bit);
+            for (int r = r0 + 1; r < r0 + RUN; ++r)
+                least = min(least, smin[r]);
+            if (__builtin_amdgcn_ballot_w64(low_seg(least)) == 0u)
+                continue;   // the whole wave: no such element
+            const int kk = seg_k(tid, r0);
+            uint32_t word = 0u;
+            if constexpr (KCONTIG) {
+                uint32_t tiny = 0xFFFFFFFFu;   // least exponent field less 1, zero and denormal wrapped to the top
+#pragma unroll
+                for (int c = 3; c >= 0; --c) {
+                    uint32_t ex = 0xFFFFFFFFu;
+#pragma unroll
+                    for (int r = 0; r < L; ++r) {
+                        const uint32_t e = element(r, c) & kExpMask;
+                        ex = min(ex, e);
+                        tiny = min(tiny, e - kMinNormal);
+                    }
+                    // word << 1, with the sign of ex - (64 << 23) shifted in
+                    word = __builtin_amdgcn_alignbit(word, ex - (64u << 23), 31);
+                }
+                if (tiny < (63u << 23)) {
+#pragma unroll
+                    for (int r = 0; r < L; ++r)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            word |= tiny_normal(element(r, c)) ? 0x10000u << c : 0u;
+                }
+                word <<= kk % KPG;
+            } else {
+#pragma unroll
+                for (int r = r0; r < r0 + RUN; ++r) {
+                    const uint32_t bit = 1u << (seg_k(tid, r) % KPG);
+                    if (low_seg(smin[r])) {
+                        word |= bit;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            word |= tiny_normal(element(r, c)) ? bit << 16 : 0u;
                     }
                 }
             }
+            word |= __builtin_amdgcn_update_dpp(0u, word, 0xB1, 0xF, 0xF, true);    // lane ^ 1
+            word |= __builtin_amdgcn_update_dpp(0u, word, 0x4E, 0xF, 0xF, true);    // lane ^ 2
+            word |= __builtin_amdgcn_update_dpp(0u, word, 0x141, 0xF, 0xF, true);   // mirrored in eight lanes
+            if ((tid & 7) == 0 && word != 0u)
+                atomicOr(&mask[(kk / KPG) * slots + slot_of(seg_o(tid, 0))], word);
         }
+    }
+
+    __device__ __forceinline__ uint32_t element(int r, int c) const {
+        return c == 0 ? v[r].x : c == 1 ? v[r].y : c == 2 ? v[r].z : v[r].w;
+    }
+    // A normal number with exponent field below 64.
+    static __device__ __forceinline__ bool tiny_normal(uint32_t u) {
+        return (u & kExpMask) - kMinNormal < (63u << 23);
     }
 };
 

@@ -80,12 +80,12 @@
 
 namespace pamk {
 
-// One micro-tile row of an S2 or S3 step from A's own encoding a: first
-// 1 + M_A (exponent field 127, a's mantissa) and +-2^E_A (a with its mantissa
+// One micro-tile row of an S3 step from A's own encoding a: first 1 + M_A
+// (exponent field 127, a's mantissa) and +-2^E_A (a with its mantissa
 // cleared, +-0 for zero / denormal a), then the SCALED products with the
-// eight b' values.  S2: acc[j] = fma(aM + b'[j], m, acc[j]); S3: the product
-// rounded on its own (an underflowing product flushes to zero), then added.
-// One asm block per row keeps the derived values' lifetime to the row.
+// eight b' values, each rounded on its own (an underflowing product flushes
+// to zero), then added.  One asm block per row keeps the derived values'
+// lifetime to the row.
 #define PAM_DMA_ROW_OPERANDS                                                                               \
     : [am] "=&v"(am), [m] "=&v"(m), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3),       \
       [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6), [t7] "=&v"(t7), [c0] "+v"(acc[0]), [c1] "+v"(acc[1]), \
@@ -100,16 +100,6 @@ namespace pamk {
     "v_add_u32 %[t2], %[am], %[b2]\n\tv_add_u32 %[t3], %[am], %[b3]\n\t"                                   \
     "v_add_u32 %[t4], %[am], %[b4]\n\tv_add_u32 %[t5], %[am], %[b5]\n\t"                                   \
     "v_add_u32 %[t6], %[am], %[b6]\n\tv_add_u32 %[t7], %[am], %[b7]\n\t"
-
-__device__ __forceinline__ void dma_s2_row(float (&acc)[8], uint32_t a, const uint32_t (&bb)[8]) {
-    uint32_t am, m, t0, t1, t2, t3, t4, t5, t6, t7;
-    asm(PAM_DMA_ROW_HEAD
-        "v_fmac_f32 %[c0], %[t0], %[m]\n\tv_fmac_f32 %[c1], %[t1], %[m]\n\t"
-        "v_fmac_f32 %[c2], %[t2], %[m]\n\tv_fmac_f32 %[c3], %[t3], %[m]\n\t"
-        "v_fmac_f32 %[c4], %[t4], %[m]\n\tv_fmac_f32 %[c5], %[t5], %[m]\n\t"
-        "v_fmac_f32 %[c6], %[t6], %[m]\n\tv_fmac_f32 %[c7], %[t7], %[m]"
-        PAM_DMA_ROW_OPERANDS);
-}
 
 __device__ __forceinline__ void dma_s3_row(float (&acc)[8], uint32_t a, const uint32_t (&bb)[8]) {
     uint32_t am, m, t0, t1, t2, t3, t4, t5, t6, t7;
@@ -156,6 +146,35 @@ __device__ __forceinline__ void dma_s1_step(float (&acc)[8][8], const uint4 &al,
           [b4] "v"(bb[4]), [b5] "v"(bb[5]), [b6] "v"(bb[6]), [b7] "v"(bb[7]));
 }
 #undef PAM_DMA_S1_ROW
+
+// A whole S2 step, acc[i][j] = fma(aM_i + b'_j, m_i, acc[i][j]): per row +-2^E_A and 1 + M_A
+// (three full-rate ops; 1.0 is the bias), then the SCALED products.
+#define PAM_DMA_S2_ROW(R, A)                                                                               \
+    "v_and_b32 %[m], 0xff800000, %[" #A "]\n\tv_xor_b32 %[am], %[m], %[" #A "]\n\t"                        \
+    "v_or_b32 %[am], 1.0, %[am]\n\t"                                                                       \
+    "v_add_u32 %[t0], %[am], %[b0]\n\tv_add_u32 %[t1], %[am], %[b1]\n\t"                                   \
+    "v_add_u32 %[t2], %[am], %[b2]\n\tv_add_u32 %[t3], %[am], %[b3]\n\t"                                   \
+    "v_add_u32 %[t4], %[am], %[b4]\n\tv_add_u32 %[t5], %[am], %[b5]\n\t"                                   \
+    "v_add_u32 %[t6], %[am], %[b6]\n\tv_add_u32 %[t7], %[am], %[b7]\n\t"                                   \
+    "v_fmac_f32 %[c" #R "0], %[t0], %[m]\n\tv_fmac_f32 %[c" #R "1], %[t1], %[m]\n\t"                       \
+    "v_fmac_f32 %[c" #R "2], %[t2], %[m]\n\tv_fmac_f32 %[c" #R "3], %[t3], %[m]\n\t"                       \
+    "v_fmac_f32 %[c" #R "4], %[t4], %[m]\n\tv_fmac_f32 %[c" #R "5], %[t5], %[m]\n\t"                       \
+    "v_fmac_f32 %[c" #R "6], %[t6], %[m]\n\tv_fmac_f32 %[c" #R "7], %[t7], %[m]\n\t"
+
+__device__ __forceinline__ void dma_s2_step(float (&acc)[8][8], const uint4 &al, const uint4 &ah,
+                                            const uint32_t (&bb)[8]) {
+    uint32_t am, m, t0, t1, t2, t3, t4, t5, t6, t7;
+    asm(PAM_DMA_S2_ROW(0, a0) PAM_DMA_S2_ROW(1, a1) PAM_DMA_S2_ROW(2, a2) PAM_DMA_S2_ROW(3, a3)
+            PAM_DMA_S2_ROW(4, a4) PAM_DMA_S2_ROW(5, a5) PAM_DMA_S2_ROW(6, a6) PAM_DMA_S2_ROW(7, a7)
+        : PAM_DMA_ACC_ROW(0), PAM_DMA_ACC_ROW(1), PAM_DMA_ACC_ROW(2), PAM_DMA_ACC_ROW(3), PAM_DMA_ACC_ROW(4),
+          PAM_DMA_ACC_ROW(5), PAM_DMA_ACC_ROW(6), PAM_DMA_ACC_ROW(7), [am] "=&v"(am), [m] "=&v"(m), [t0] "=&v"(t0),
+          [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6),
+          [t7] "=&v"(t7)
+        : [a0] "v"(al.x), [a1] "v"(al.y), [a2] "v"(al.z), [a3] "v"(al.w), [a4] "v"(ah.x), [a5] "v"(ah.y),
+          [a6] "v"(ah.z), [a7] "v"(ah.w), [b0] "v"(bb[0]), [b1] "v"(bb[1]), [b2] "v"(bb[2]), [b3] "v"(bb[3]),
+          [b4] "v"(bb[4]), [b5] "v"(bb[5]), [b6] "v"(bb[6]), [b7] "v"(bb[7]));
+}
+#undef PAM_DMA_S2_ROW
 #undef PAM_DMA_ACC_ROW
 
 // Eight values of one k row of a compute buffer: four at p, four at p + half.
@@ -175,6 +194,15 @@ constexpr int dma_waves_per_simd(int bm, int bn, int kw) {
 // k steps per k-group per LDS chunk: the same for every tile shape (the
 // step masks hold one bit per step of a chunk in each half of a 32-bit word).
 constexpr int dma_kpg(int, int, int) { return kChunkK; }
+
+// A chunk with more S2 steps than this (zeros in most of its k steps: ReLU
+// activations, masked probabilities, dropout) takes its S1 and S2 steps in
+// one unrolled pass of S2 steps, operands read one step ahead; with fewer,
+// the S2 steps come one by one after the S1 pass.  A ReLU block's six products
+// (8192 tokens, 512 -> 2048 -> 512, four of them on half-zero operands) took
+// 2346 us; 2317 us with this pass, 2112 us with the step masks combined over
+// lanes as well (DmaTile::mark).
+constexpr int kDenseS2 = 8;
 
 // Minimum LDS words per workgroup.  Workgroups of one or two waves can be
 // placed unevenly on a compute unit's four SIMDs when more fit than the
@@ -330,8 +358,10 @@ pam_gemm_dma_kernel(GemmParams p) {
             lb.flush_denormals();
         uint32_t *mask = sMask[c & 1];
         __syncthreads();   // every wave is done reading the previous chunk (and zeroing this mask)
-        la.template store<KPG>(encA, false, tid_c, smin_a, mask, NSLOT, a_slot);
-        lb.template store<KPG>(encB, true, tid_c, smin_b, mask, NSLOT, b_slot);
+        la.store_values(encA, false, tid_c);
+        la.template mark<KPG>(tid_c, smin_a, mask, NSLOT, a_slot);
+        lb.store_values(encB, true, tid_c);
+        lb.template mark<KPG>(tid_c, smin_b, mask, NSLOT, b_slot);
         // The workgroup's SPECIAL vote: one more mask word.
         if (mx >= (191u << 24))
             atomicOr(&mask[KW * NSLOT], 1u);
@@ -354,8 +384,8 @@ pam_gemm_dma_kernel(GemmParams p) {
 
         // The group's steps of this chunk (those past K take none).
         const uint32_t steps = (1u << (EDGE ? min(max(k_rem - k_first, 0), KPG) : KPG)) - 1u;
-        const uint32_t s1_bits = special ? 0u : (~low & steps);
-        const uint32_t s2_bits = special ? 0u : (low & ~(low >> 16) & steps);
+        uint32_t s1_bits = special ? 0u : (~low & steps);
+        uint32_t s2_bits = special ? 0u : (low & ~(low >> 16) & steps);
         const uint32_t s3_bits = special ? 0u : ((low >> 16) & steps);
         const uint32_t sp_bits = special ? steps : 0u;
         const uint32_t *a_row = encA + k_first * BM + ty * 4;
@@ -371,6 +401,22 @@ pam_gemm_dma_kernel(GemmParams p) {
                 bq[slot][0] = lo.x; bq[slot][1] = lo.y; bq[slot][2] = lo.z; bq[slot][3] = lo.w;
                 bq[slot][4] = hi.x; bq[slot][5] = hi.y; bq[slot][6] = hi.z; bq[slot][7] = hi.w;
             };
+            if (__builtin_popcount(s2_bits) > kDenseS2) {
+                s2_bits |= s1_bits;
+                rd(0, 0);
+#pragma unroll
+                for (int k = 0; k < KPG; ++k) {
+                    const int cur = k & 1;
+                    if (k + 1 < KPG)
+                        rd(k + 1, cur ^ 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if ((s2_bits >> k) & 1u)
+                        dma_s2_step(acc, al[cur], ah[cur], bq[cur]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                s1_bits = 0u;
+                s2_bits = 0u;
+            }
             if (s1_bits != 0u) {
                 rd(0, 0);
 #pragma unroll
@@ -385,15 +431,14 @@ pam_gemm_dma_kernel(GemmParams p) {
                 }
             }
         }
-        // S2 steps, then S3 steps (1 + M_A and +-2^E_A derived per row).
+        // S2 steps, then S3 steps.
         for (uint32_t todo = s2_bits; todo != 0u; todo &= todo - 1u) {
             const int kk = __builtin_ctz(todo);
-            uint32_t aa[8], bb[8];
-            dma_frag(a_row + kk * BM, HM, aa);
+            const uint4 al = *reinterpret_cast<const uint4 *>(a_row + kk * BM);
+            const uint4 ah = *reinterpret_cast<const uint4 *>(a_row + kk * BM + HM);
+            uint32_t bb[8];
             dma_frag(b_row + kk * BN, HN, bb);
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                dma_s2_row(acc[i], aa[i], bb);
+            dma_s2_step(acc, al, ah, bb);
         }
         for (uint32_t todo = s3_bits; todo != 0u; todo &= todo - 1u) {
             const int kk = __builtin_ctz(todo);

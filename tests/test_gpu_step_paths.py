@@ -55,3 +55,29 @@ def test_every_two_op_step_count(ta, tb, plan):
                                batches=[0])
     check_gemm(c.cpu().numpy(), c_ref, s_ref, K, f"step paths ta={ta} tb={tb} plan={plan}")
 
+
+
+@pytest.mark.parametrize("share", [0.01, 0.1, 0.5, 1.0])
+@pytest.mark.parametrize("plan", [(128, 128, 1, 1, 0), (128, 64, 1, 1, 0), (128, 64, 1, 2, 0), (64, 64, 1, 1, 0),
+                                  (64, 64, 1, 4, 0)])
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+def test_dense_zeros_with_tiny_values(ta, tb, plan, share):
+    """Zeros in this share of A's and B's elements (from a few steps a chunk
+    to all of them on the add + fma path, singly or in one pass), a few
+    denormals among them, and in A's first 40 rows and B's first 40 columns
+    tiny normals, whose steps round each product on its own."""
+    g = np.random.default_rng(int(share * 100))
+    a, b = g.standard_normal((M, K)).astype(np.float32), g.standard_normal((K, N)).astype(np.float32)
+    for x in (a, b):
+        u = g.random(x.shape)
+        x[u < share] = 0.0
+        x[u < share / 50] = 1e-40
+    a[:40][g.random((40, K)) < 0.01] = TINY
+    b[:, :40][g.random((K, 40)) < 0.01] = -TINY
+    note(f"dense zeros share={share} ta={ta} tb={tb} plan={plan}")
+    a_buf = np.ascontiguousarray(a.T if ta else a)
+    b_buf = np.ascontiguousarray(b.T if tb else b)
+    c = pam.bmm(to_dev(a_buf)[None], to_dev(b_buf)[None], trans_a=ta, trans_b=tb, plan=plan)
+    c_ref, s_ref = oracle_gemm(a_buf.ravel(), b_buf.ravel(), ta, tb, M, N, K, a_buf.shape[1], b_buf.shape[1],
+                               batches=[0])
+    check_gemm(c.cpu().numpy(), c_ref, s_ref, K, f"dense zeros share={share}")
