@@ -383,12 +383,21 @@ pam_status_t check_workspace(const Workspace *ws, size_t need) {
     return PAM_SUCCESS;
 }
 
-// The product under `plan`; a split plan keeps its partial sums in `ext`,
+// Products that the skinny kernel takes in place of their plan: few rows of
+// op(A) or columns of op(B), both operands K-contiguous.
+bool skinny_product(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t batch) {
+    if (ta != PAM_OP_N || tb != PAM_OP_T || std::min(m, n) > pamk::kSkinnyRows)
+        return false;
+    return batch <= pamk::kMaxSkinnyItems / (ceil_div(std::max(m, n), 16) * 8);
+}
+
+// The product under `plan` (unless forced, skinny products take their own
+// kernel); a split plan keeps its partial sums in `ext`,
 // which must hold the plan's workspace bytes.  Allocates nothing.
 pam_status_t run_gemm(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t k, const float *A, int64_t lda,
                       int64_t sa, const float *B, int64_t ldb, int64_t sb, float *C, int64_t ldc, int64_t sc,
                       int64_t batch, const Plan &plan, hipStream_t stream, int round_drop = 0,
-                      const Workspace *ext = nullptr, bool bf16 = false) {
+                      const Workspace *ext = nullptr, bool bf16 = false, bool forced_plan = false) {
     if (m == 0 || n == 0 || batch == 0)
         return PAM_SUCCESS;
     Layout L{};
@@ -425,6 +434,13 @@ pam_status_t run_gemm(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t k,
     p.splits = (int32_t)L.splits;
     float *ws = L.ws_bytes > 0 ? static_cast<float *>(ext->ptr) : nullptr;
 
+    if (!forced_plan && skinny_product(ta, tb, m, n, batch)) {
+        p.A = A;
+        p.B = B;
+        p.C = C;
+        const hipError_t e = pamk::launch_pam_skinny(m <= pamk::kSkinnyRows, bf16, p, batch, stream);
+        return e == hipSuccess ? PAM_SUCCESS : fail_hip(e, "skinny product kernel launch");
+    }
     for (int64_t b0 = 0; b0 < batch; b0 += L.per_launch) {
         const int64_t nb = std::min(L.per_launch, batch - b0);
         const size_t es = bf16 ? 2 : 4;   // operand element bytes
@@ -938,7 +954,7 @@ pam_status_t pam_gemm_batched_with_plan(pam_op_t transA, pam_op_t transB, int64_
         return PAM_SUCCESS;
     const Workspace ws{workspace, workspace_bytes};
     return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, p, stream, 0,
-                    &ws);
+                    &ws, false, true);
 }
 
 pam_status_t pam_device_info(int device, pam_device_info_t *info) {

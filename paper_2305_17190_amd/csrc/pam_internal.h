@@ -56,6 +56,13 @@ hipError_t launch_round_mantissa(const float *a, float *out, int64_t n, int drop
 hipError_t launch_pam_gemm(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
                            const GemmParams &p, hipStream_t stream);
 
+// Products of K-contiguous operands (op N, op T) with at most kSkinnyRows rows
+// of op(A) (rows) or columns of op(B) (otherwise): pam_skinny.hip.  One launch
+// for the batch; takes no plan and no workspace.
+constexpr int kSkinnyRows = 32;
+constexpr int64_t kMaxSkinnyItems = 8388607;   // workgroups of 512 threads: below 2^32 threads
+hipError_t launch_pam_skinny(bool rows, bool bf16, const GemmParams &p, int64_t batch, hipStream_t stream);
+
 // The kernel behind launch_pam_gemm (pam_gemm_dma.hip): operand chunks
 // copied into LDS by the memory pipeline.
 hipError_t launch_pam_gemm_dma(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,

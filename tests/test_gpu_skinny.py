@@ -1,0 +1,98 @@
+"""Products with few rows of op(A) or columns of op(B), both K-contiguous:
+their own kernel, against the oracle and against the tiled path (the same
+product with its plan forced), over row counts around its blocks of 4, 8 and
+16, ragged widths and K, element types, mantissa bits, batches and strides,
+unaligned views, and operand values of every class."""
+import numpy as np
+import pytest
+
+import paper_2305_17190_amd as pam
+import pam_workloads as wl
+from gpu_util import check_gemm, device, note, oracle_gemm, to_dev
+from oracle import pam_ref
+
+pytestmark = pytest.mark.gpu
+
+
+def run_both(a, b, bits=23):
+    """The product by the library's choice and by its forced plan."""
+    import torch
+    m, k = a.shape[1:]
+    n = b.shape[1]
+    c = pam.bmm(a, b, trans_b=True, mantissa_bits=bits)
+    tiled = pam.bmm(a, b, trans_b=True, plan=pam.plan(m, n, k, a.shape[0])) \
+        if bits == 23 and a.dtype == torch.float32 else None
+    return c.cpu().numpy(), None if tiled is None else tiled.cpu().numpy()
+
+
+@pytest.mark.parametrize("few", [1, 3, 4, 5, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("wide,k", [(1, 1), (15, 63), (17, 64), (130, 65), (300, 515), (64, 1030)])
+@pytest.mark.parametrize("swap", [False, True])
+def test_row_counts_widths_and_k(few, wide, k, swap):
+    m, n = (wide, few) if swap else (few, wide)
+    g = np.random.default_rng(1000 + few + wide + k)
+    a, b = g.standard_normal((m, k)).astype(np.float32), g.standard_normal((n, k)).astype(np.float32)
+    a[g.random(a.shape) < 0.2] = 0.0
+    note(f"skinny m={m} n={n} k={k}")
+    c, tiled = run_both(to_dev(a)[None], to_dev(b)[None])
+    c_ref, s_ref = oracle_gemm(a.ravel(), b.ravel(), False, True, m, n, k, k, k, batches=[0])
+    check_gemm(c, c_ref, s_ref, k, "skinny")
+    check_gemm(tiled, c_ref, s_ref, k, "tiled")
+
+
+@pytest.mark.parametrize("few", [2, 7, 12])
+@pytest.mark.parametrize("bits", [23, 7, 3])
+def test_batches_strides_and_narrow_mantissas(few, bits):
+    import torch
+    batch, n, k = 5, 70, 90
+    g = np.random.default_rng(1100 + few + bits)
+    a = g.standard_normal((batch, few, k)).astype(np.float32)
+    b = g.standard_normal((batch, n, k)).astype(np.float32)
+    note(f"skinny batch few={few} bits={bits}")
+    # rows one element past alignment, gaps between rows and matrices
+    abuf = torch.full((batch, few + 1, k + 3), float("nan"), device=device())
+    abuf[:, :few, 1:k + 1] = to_dev(a)
+    bbuf = torch.full((batch, n + 2, k + 1), float("nan"), device=device())
+    bbuf[:, :n, :k] = to_dev(b)
+    out = torch.full((batch, few, n + 1), float("nan"), device=device())[:, :, :n]
+    pam.bmm(abuf[:, :few, 1:k + 1], bbuf[:, :n, :k], trans_b=True, out=out, mantissa_bits=bits)
+    ar, br = (a, b) if bits == 23 else (pam_ref.round_mantissa_ref(x, bits) for x in (a, b))
+    c_ref, s_ref = oracle_gemm(ar, br, False, True, few, n, k, k, k, few * k, n * k, batches=list(range(batch)))
+    check_gemm(out.cpu().numpy(), c_ref, s_ref, k, f"skinny batch bits={bits}")
+    # a zero stride broadcasts an operand
+    one = pam.bmm(abuf[:1, :few, 1:k + 1].expand(batch, few, k), bbuf[:, :n, :k], trans_b=True, mantissa_bits=bits)
+    assert torch.equal(one[0].view(torch.int32), out[0].contiguous().view(torch.int32))
+
+
+@pytest.mark.parametrize("few,n,k", [(1, 40, 700), (6, 33, 130), (16, 260, 77)])
+def test_bf16_equals_the_widened_product(few, n, k):
+    import torch
+    g = torch.Generator().manual_seed(1200 + few)
+    a = torch.randn((few, k), generator=g).to(torch.bfloat16).to(device())
+    b = torch.randn((n, k), generator=g).to(torch.bfloat16).to(device())
+    note(f"skinny bf16 few={few} n={n} k={k}")
+    for x, y in ((a, b), (b, a)):
+        c16, c32 = pam.gemm(x, y, trans_b=True), pam.gemm(x.float(), y.float(), trans_b=True)
+        assert torch.equal(c16.view(torch.int32), c32.view(torch.int32))
+
+
+@pytest.mark.parametrize("few", [1, 4, 11])
+@pytest.mark.parametrize("kind", ["finite", "huge", "nonfinite"])
+def test_every_operand_class(few, kind):
+    """Zeros, denormals, tiny and boundary values; then |x| >= 2^64 up to
+    FLT_MAX; then inf and NaN too."""
+    n, k = 50, 150
+    g = np.random.default_rng(1300 + few)
+    pats = wl.special_bit_patterns()
+    mag = np.abs(pats)
+    pats = pats[mag < 2.0 ** 64] if kind == "finite" else pats[np.isfinite(pats)] if kind == "huge" else pats
+    a = g.standard_normal((few, k)).astype(np.float32)
+    b = g.standard_normal((n, k)).astype(np.float32)
+    for x in (a, b):
+        pick = g.random(x.shape) < (0.3 if kind == "finite" else 0.02)
+        x[pick] = g.choice(pats, size=int(pick.sum()))
+    note(f"skinny classes few={few} kind={kind}")
+    c_ref, s_ref = oracle_gemm(a.ravel(), b.ravel(), False, True, few, n, k, k, k, batches=[0])
+    c, tiled = run_both(to_dev(a)[None], to_dev(b)[None])
+    check_gemm(c, c_ref, s_ref, k, f"skinny {kind}")
+    check_gemm(tiled, c_ref, s_ref, k, f"tiled {kind}")
