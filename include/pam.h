@@ -162,10 +162,11 @@ typedef struct {
 } pam_plan_t;
 
 /* The plan pam_gemm_batched_ws (and pam_gemm_workspace_size) uses for these
- * sizes, split K allowed.  m, n, batch > 0; k >= 0.  Products whose operands
- * are both K-contiguous (op N, op T) with at most 32 rows of op(A) or columns
- * of op(B) run a kernel without a plan instead, unless pam_gemm_batched_with_plan
- * forces one: the same product, up to float32 summation order. */
+ * sizes, split K allowed.  m, n, batch > 0; k >= 0.  Two kinds of product run
+ * a kernel without a plan instead (the same product, up to float32 summation
+ * order): those whose operands are both K-contiguous (op N, op T) with at
+ * most 32 rows of op(A) or columns of op(B), and small ones whose plan would
+ * leave most of the GPU idle. */
 pam_status_t pam_gemm_plan(int64_t m, int64_t n, int64_t k, int64_t batch, pam_plan_t *plan);
 
 /* The fastest plan (by the library's cost model) whose split-K partial sums
@@ -178,7 +179,9 @@ pam_status_t pam_gemm_plan_for_workspace(int64_t m, int64_t n, int64_t k, int64_
  * pam_gemm_batched with an explicit plan (for tests and tuning).
  * (tile_m, tile_n, kgroups) is (128,128,1), (128,64,1), (128,64,2),
  * (64,64,1) or (64,64,4); 1 <= splits <= 64; whole_tiles >= 0.  The result is
- * the same product as with the automatic plan, up to float32 summation order.
+ * the same product as with the automatic plan, up to float32 summation order;
+ * with a plan equal to pam_gemm_plan's, or pam_gemm_plan_for_workspace's for 0
+ * bytes, bit for bit what the automatic entry points give.
  * A plan that splits K keeps its partial sums in `workspace`: device memory
  * of workspace_bytes >= pam_gemm_plan_workspace_size's value, 16-byte aligned,
  * that nothing else touches until this call's kernels on `stream` are done

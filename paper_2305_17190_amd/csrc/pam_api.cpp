@@ -99,6 +99,8 @@ constexpr int64_t kMaxHybridTiles = 1 << 20;
 // Shortest K for which one full round of whole-K 128 x 128 tiles is replaced
 // by the quarter-round hybrid plan (choose_plan).
 constexpr int64_t kOneRoundHybridMinK = 512;
+// Most 32 x 32 tiles of a small product (small_product).
+constexpr int64_t kMaxSmallTiles = 2048;
 // Split counts the plan search considers.
 constexpr int kSplitChoices[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48, 56, 64};
 
@@ -383,6 +385,11 @@ pam_status_t check_workspace(const Workspace *ws, size_t need) {
     return PAM_SUCCESS;
 }
 
+bool same_plan(const Plan &a, const Plan &b) {
+    return a.tile_m == b.tile_m && a.tile_n == b.tile_n && a.kgroups == b.kgroups && a.splits == b.splits &&
+           a.whole_tiles == b.whole_tiles;
+}
+
 // Products that the skinny kernel takes in place of their plan: few rows of
 // op(A) or columns of op(B), both operands K-contiguous.
 bool skinny_product(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t batch) {
@@ -391,8 +398,26 @@ bool skinny_product(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t batc
     return batch <= pamk::kMaxSkinnyItems / (ceil_div(std::max(m, n), 16) * 8);
 }
 
-// The product under `plan` (unless forced, skinny products take their own
-// kernel); a split plan keeps its partial sums in `ext`,
+// Products that the small-product kernel takes in place of their plan: when
+// its time is well below the plan's estimate (by 0.8: the estimates of split
+// plans on few tiles run 20-30% high).  Its time, measured: 3.6 us, and per
+// 128 k steps 1.9 us up to 256 tiles of 32 x 32, then 6.7 us per 1024 of them.
+// Only in place of pam_gemm_plan's plan: a product whose plan its workspace
+// limits keeps that plan.
+bool small_product(const Plan &plan, int64_t m, int64_t n, int64_t k, int64_t batch) {
+    const int64_t tiles = ceil_div(m, 32) * ceil_div(n, 32) * batch;
+    if (tiles > kMaxSmallTiles || !same_plan(plan, choose_plan(m, n, k, batch, kAnyWorkspace)))
+        return false;
+    const double chunks = double(ceil_div(k, pamk::kChunkK * pamk::kSmallWaves));
+    const double small_s = 3.6e-6 + chunks * std::max(1.9e-6, 6.7e-6 * double(tiles) / 1024.0);
+    for (const auto &c : kShapes)
+        if (c.bm == plan.tile_m && c.bn == plan.tile_n && c.kw == plan.kgroups)
+            return small_s < 0.8 * plan_time(c, plan, m, n, k, batch);
+    return false;
+}
+
+// The product under `plan` (unless forced, skinny and small products take
+// their own kernels); a split plan keeps its partial sums in `ext`,
 // which must hold the plan's workspace bytes.  Allocates nothing.
 pam_status_t run_gemm(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t k, const float *A, int64_t lda,
                       int64_t sa, const float *B, int64_t ldb, int64_t sb, float *C, int64_t ldc, int64_t sc,
@@ -440,6 +465,13 @@ pam_status_t run_gemm(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t k,
         p.C = C;
         const hipError_t e = pamk::launch_pam_skinny(m <= pamk::kSkinnyRows, bf16, p, batch, stream);
         return e == hipSuccess ? PAM_SUCCESS : fail_hip(e, "skinny product kernel launch");
+    }
+    if (!forced_plan && small_product(plan, m, n, k, batch)) {
+        p.A = A;
+        p.B = B;
+        p.C = C;
+        const hipError_t e = pamk::launch_pam_small(ta == PAM_OP_T, tb == PAM_OP_T, bf16, p, batch, stream);
+        return e == hipSuccess ? PAM_SUCCESS : fail_hip(e, "small product kernel launch");
     }
     for (int64_t b0 = 0; b0 < batch; b0 += L.per_launch) {
         const int64_t nb = std::min(L.per_launch, batch - b0);
@@ -952,9 +984,14 @@ pam_status_t pam_gemm_batched_with_plan(pam_op_t transA, pam_op_t transB, int64_
         return st;
     if (m == 0 || n == 0 || batch == 0)
         return PAM_SUCCESS;
+    // A plan the library would pick itself runs as the library runs it.
+    const Plan given{plan->tile_m, plan->tile_n, plan->kgroups, plan->splits, 0, plan->whole_tiles};
+    const int64_t k1 = std::max<int64_t>(k, 1);
+    const bool forced = !same_plan(given, choose_plan(m, n, k1, batch, kAnyWorkspace)) &&
+                        !same_plan(given, choose_plan(m, n, k1, batch, 0));
     const Workspace ws{workspace, workspace_bytes};
     return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, p, stream, 0,
-                    &ws, false, true);
+                    &ws, false, forced);
 }
 
 pam_status_t pam_device_info(int device, pam_device_info_t *info) {

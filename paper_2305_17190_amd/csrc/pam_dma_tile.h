@@ -260,6 +260,12 @@ struct DmaTile {
         for (int r = 0; r < L; ++r) {
             const int o = seg_o(tid, r);
             const int kk = seg_k(tid, r);
+            const bool unmoved = KCONTIG ? (kk & -EPC) + EPC <= k_rem
+                                         : kk < k_rem && (o & -EPC) + EPC <= o_lim - o0;
+            if (unmoved) {   // its piece lies where it does inside the operand
+                v[r] = read_slot(raw, slot_of(w, tid & 63, r));
+                continue;
+            }
             uint32_t e[4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -425,6 +431,17 @@ struct DmaTile {
             if ((tid & 7) == 0 && word != 0u)
                 atomicOr(&mask[(kk / KPG) * slots + slot_of(seg_o(tid, 0))], word);
         }
+    }
+
+    // Some held element is a tiny normal.
+    __device__ __forceinline__ bool any_tiny() const {
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < L; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                any = any || tiny_normal(element(r, c));
+        return any;
     }
 
     __device__ __forceinline__ uint32_t element(int r, int c) const {

@@ -63,6 +63,11 @@ constexpr int kSkinnyRows = 32;
 constexpr int64_t kMaxSkinnyItems = 8388607;   // workgroups of 512 threads: below 2^32 threads
 hipError_t launch_pam_skinny(bool rows, bool bf16, const GemmParams &p, int64_t batch, hipStream_t stream);
 
+// Small products (pam_small.hip): 32 x 32 tiles, kSmallWaves waves sharing each
+// chunk's k steps.  One launch for the batch; takes no plan and no workspace.
+constexpr int kSmallWaves = 8;
+hipError_t launch_pam_small(bool trans_a, bool trans_b, bool bf16, GemmParams p, int64_t batch, hipStream_t stream);
+
 // The kernel behind launch_pam_gemm (pam_gemm_dma.hip): operand chunks
 // copied into LDS by the memory pipeline.
 hipError_t launch_pam_gemm_dma(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,

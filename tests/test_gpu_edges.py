@@ -11,7 +11,9 @@ from gpu_util import check_gemm, device, note, oracle_gemm, to_dev
 
 pytestmark = pytest.mark.gpu
 
-PLANS = [(128, 128, 1, 1, 0), (128, 64, 1, 1, 0), (128, 64, 1, 2, 0), (64, 64, 1, 1, 0), (64, 64, 1, 4, 0)]
+# (A whole-tile count beside one split changes nothing but keeps the plan from
+# being the library's own, which a small product would not run.)
+PLANS = [(128, 128, 1, 1, 1), (128, 64, 1, 1, 1), (128, 64, 1, 2, 1), (64, 64, 1, 1, 1), (64, 64, 1, 4, 1)]
 
 
 def placed(x, shift, gap, dtype):

@@ -1,6 +1,6 @@
 """Products with few rows of op(A) or columns of op(B), both K-contiguous:
 their own kernel, against the oracle and against the tiled path (the same
-product with its plan forced), over row counts around its blocks of 4, 8 and
+product with another plan forced), over row counts around its blocks of 4, 8 and
 16, ragged widths and K, element types, mantissa bits, batches and strides,
 unaligned views, and operand values of every class."""
 import numpy as np
@@ -15,14 +15,11 @@ pytestmark = pytest.mark.gpu
 
 
 def run_both(a, b, bits=23):
-    """The product by the library's choice and by its forced plan."""
-    import torch
-    m, k = a.shape[1:]
-    n = b.shape[1]
+    """The product by the library's choice and by a forced plan (which, with a
+    whole-tile count, is no plan of the library's own)."""
     c = pam.bmm(a, b, trans_b=True, mantissa_bits=bits)
-    tiled = pam.bmm(a, b, trans_b=True, plan=pam.plan(m, n, k, a.shape[0])) \
-        if bits == 23 and a.dtype == torch.float32 else None
-    return c.cpu().numpy(), None if tiled is None else tiled.cpu().numpy()
+    tiled = pam.bmm(a, b, trans_b=True, plan=(64, 64, 1, 4, 1))
+    return c.cpu().numpy(), tiled.cpu().numpy()
 
 
 @pytest.mark.parametrize("few", [1, 3, 4, 5, 8, 9, 16, 17, 32, 33])
@@ -79,16 +76,17 @@ def test_bf16_equals_the_widened_product(few, n, k):
 @pytest.mark.parametrize("few", [1, 4, 11])
 @pytest.mark.parametrize("kind", ["finite", "huge", "nonfinite"])
 def test_every_operand_class(few, kind):
-    """Zeros, denormals, tiny and boundary values; then |x| >= 2^64 up to
-    FLT_MAX; then inf and NaN too."""
+    """Zeros, denormals, tiny and boundary values; then |x| >= 2^64 (in A only:
+    no partial sum overflows); then inf and NaN too."""
     n, k = 50, 150
     g = np.random.default_rng(1300 + few)
     pats = wl.special_bit_patterns()
     mag = np.abs(pats)
-    pats = pats[mag < 2.0 ** 64] if kind == "finite" else pats[np.isfinite(pats)] if kind == "huge" else pats
+    pats = pats[mag < 2.0 ** 64] if kind == "finite" else pats[mag < 2.0 ** 66] if kind == "huge" else \
+        pats[~((mag >= 2.0 ** 64) & np.isfinite(pats))]
     a = g.standard_normal((few, k)).astype(np.float32)
     b = g.standard_normal((n, k)).astype(np.float32)
-    for x in (a, b):
+    for x in (a, b) if kind != "huge" else (a,):
         pick = g.random(x.shape) < (0.3 if kind == "finite" else 0.02)
         x[pick] = g.choice(pats, size=int(pick.sum()))
     note(f"skinny classes few={few} kind={kind}")

@@ -1,0 +1,108 @@
+"""Small products (32 x 32 tiles, eight waves sharing each chunk of 128 k
+steps): sizes around the tiles and chunks, every layout and element type,
+batches with strides and broadcasts, unaligned views, mantissa rounding, and
+operand values of every class, against the oracle and against the tiled
+kernel under a forced plan."""
+import numpy as np
+import pytest
+
+import paper_2305_17190_amd as pam
+import pam_workloads as wl
+from gpu_util import check_gemm, device, note, oracle_gemm, to_dev
+from oracle import pam_ref
+
+pytestmark = pytest.mark.gpu
+
+TILED = (64, 64, 1, 4, 1)   # with its whole-tile count no plan of the library's own
+
+
+def buffers(m, n, k, ta, tb, seed, batch=1):
+    g = np.random.default_rng(seed)
+    a = g.standard_normal((batch, k, m) if ta else (batch, m, k)).astype(np.float32)
+    b = g.standard_normal((batch, n, k) if tb else (batch, k, n)).astype(np.float32)
+    return a, b
+
+
+def reference(a, b, ta, tb):
+    batch, n, k = a.shape[0], b.shape[1 if tb else 2], a.shape[1 if ta else 2]
+    m = a.shape[2 if ta else 1]
+    return oracle_gemm(a, b, ta, tb, m, n, k, a.shape[2], b.shape[2], a[0].size, b[0].size,
+                       batches=list(range(batch))) + (k,)
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("m,n,k", [(33, 33, 1), (40, 64, 15), (64, 33, 16), (65, 96, 127), (95, 97, 128), (34, 130, 129),
+                                   (128, 128, 255), (100, 50, 256), (63, 64, 700)])
+def test_sizes_and_layouts(m, n, k, ta, tb):
+    note(f"small m={m} n={n} k={k} ta={ta} tb={tb}")
+    a, b = buffers(m, n, k, ta, tb, 1400 + m + n + k)
+    c_ref, s_ref, k = reference(a, b, ta, tb)
+    ad, bd = to_dev(a), to_dev(b)
+    check_gemm(pam.bmm(ad, bd, trans_a=ta, trans_b=tb).cpu().numpy(), c_ref, s_ref, k, "small")
+    check_gemm(pam.bmm(ad, bd, trans_a=ta, trans_b=tb, plan=TILED).cpu().numpy(), c_ref, s_ref, k, "tiled")
+    # the library's own plan, forced, runs as the library does
+    import torch
+    own = pam.bmm(ad, bd, trans_a=ta, trans_b=tb, plan=pam.plan(m, n, k))
+    assert torch.equal(own.view(torch.int32), pam.bmm(ad, bd, trans_a=ta, trans_b=tb).view(torch.int32))
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("bits", [23, 7])
+def test_batches_views_and_narrow_mantissas(ta, tb, bits):
+    import torch
+    batch, m, n, k = 3, 50, 70, 90
+    note(f"small batch ta={ta} tb={tb} bits={bits}")
+    a, b = buffers(m, n, k, ta, tb, 1500, batch)
+
+    def view(x):   # one element past alignment, gaps after rows and matrices, NaN around
+        z, r, c = x.shape
+        buf = torch.full((z, r + 1, c + 3), float("nan"), device=device())
+        buf[:, :r, 1:c + 1] = to_dev(x)
+        return buf[:, :r, 1:c + 1]
+
+    out = torch.full((batch, m, n + 1), float("nan"), device=device())[:, :, :n]
+    pam.bmm(view(a), view(b), trans_a=ta, trans_b=tb, out=out, mantissa_bits=bits)
+    ar, br = (a, b) if bits == 23 else (pam_ref.round_mantissa_ref(x, bits) for x in (a, b))
+    c_ref, s_ref, _ = reference(ar, br, ta, tb)
+    check_gemm(out.cpu().numpy(), c_ref, s_ref, k, "small batch")
+    one = pam.bmm(view(a)[:1].expand(batch, *a.shape[1:]), view(b), trans_a=ta, trans_b=tb, mantissa_bits=bits)
+    assert torch.equal(one[0].view(torch.int32), out[0].contiguous().view(torch.int32))
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("m,n,k", [(64, 64, 128), (45, 77, 203), (33, 40, 5)])
+def test_bf16_equals_the_widened_product(m, n, k, ta, tb):
+    import torch
+    note(f"small bf16 m={m} n={n} k={k} ta={ta} tb={tb}")
+    a, b = buffers(m, n, k, ta, tb, 1600 + k)
+    a16, b16 = to_dev(a).to(torch.bfloat16), to_dev(b).to(torch.bfloat16)
+    c16 = pam.bmm(a16, b16, trans_a=ta, trans_b=tb)
+    c32 = pam.bmm(a16.float(), b16.float(), trans_a=ta, trans_b=tb)
+    assert torch.equal(c16.view(torch.int32), c32.view(torch.int32))
+
+
+@pytest.mark.parametrize("ta,tb", [(False, True), (True, False)])
+@pytest.mark.parametrize("kind", ["zeros", "finite", "huge", "nonfinite"])
+def test_every_operand_class(kind, ta, tb):
+    """The forms of the steps: zeros and denormals alone, with tiny values,
+    with |x| >= 2^64 (in A only: no partial sum overflows), with inf and NaN;
+    the last chunk is clean."""
+    m, n, k = 70, 66, 300
+    g = np.random.default_rng(1700)
+    pats = wl.special_bit_patterns()
+    mag = np.abs(pats)
+    pats = {"zeros": pats[mag < 2.0 ** -126], "finite": pats[mag < 2.0 ** 64],
+            "huge": np.append(pats[mag < 2.0 ** 66], np.float32([2.0 ** 64, -1.7 * 2.0 ** 64])),
+            "nonfinite": pats[~((mag >= 2.0 ** 64) & np.isfinite(pats))]}[kind]
+    a, b = buffers(m, n, k, ta, tb, 1700)
+    for x, k_axis in ((a, 1 if ta else 2), (b, 2 if tb else 1)):
+        pick = g.random(x.shape) < (0.01 if kind == "nonfinite" else 0.2)
+        if kind == "huge" and x is b:
+            continue
+        idx = np.arange(k).reshape((1, k, 1) if k_axis == 1 else (1, 1, k))
+        pick &= idx < 256
+        x[pick] = g.choice(pats, size=int(pick.sum()))
+    note(f"small classes kind={kind} ta={ta} tb={tb}")
+    c_ref, s_ref, _ = reference(a, b, ta, tb)
+    check_gemm(pam.bmm(to_dev(a), to_dev(b), trans_a=ta, trans_b=tb).cpu().numpy(), c_ref, s_ref, k, kind)
+    check_gemm(pam.bmm(to_dev(a), to_dev(b), trans_a=ta, trans_b=tb, plan=TILED).cpu().numpy(), c_ref, s_ref, k, kind)
