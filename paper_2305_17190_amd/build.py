@@ -44,7 +44,7 @@ def sources():
 
 
 # Sources compiled in parts, one object each (their count of parts).
-PARTS = {"pam_gemm_dma.hip": 4}
+PARTS = {"pam_gemm_dma.hip": 6}
 
 
 def _run(cmd, verbose: bool) -> None:

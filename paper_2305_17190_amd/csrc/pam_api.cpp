@@ -101,6 +101,9 @@ constexpr int64_t kMaxHybridTiles = 1 << 20;
 constexpr int64_t kOneRoundHybridMinK = 512;
 // Most 32 x 32 tiles of a small product (small_product).
 constexpr int64_t kMaxSmallTiles = 2048;
+// Shortest K for which a launch is taken to last at least one whole-K tile
+// (plan_time).
+constexpr int64_t kWholeTileBoundMinK = 2048;
 // Split counts the plan search considers.
 constexpr int kSplitChoices[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48, 56, 64};
 
@@ -165,6 +168,13 @@ double plan_time(const Shape &c, const Plan &p, int64_t m, int64_t n, int64_t k,
     const double wg_slice = per_chunk * double(ceil_div(p.k_per_split, bk)) + costs.workgroup_s;
     const int64_t displaced = rem > 0 ? (int64_t)std::ceil(double(rem) * wg_whole / wg_slice) : 0;
     double t = double(before) * wg_whole + rounds_time(c, split_tiles * p.splits + displaced, wg_slice, before);
+    // A whole-K tile is not divisible: where all of them start at once beside
+    // slices, one bounds the launch (1536 x 3264 x 16238 ran 6.9 ms with 56
+    // whole tiles of 312, 3.7 ms with all of them split).  For long K only:
+    // a short whole tile beside few others runs up to twice as fast as in a
+    // full compute unit, and the plans without the bound measured well there.
+    if (whole > 0 && before == 0 && k >= kWholeTileBoundMinK)
+        t = std::max(t, wg_whole);
     t += costs.split_s + double(p.splits + 1) * double(split_tiles) * c.bm * c.bn * 4.0 / costs.partial_bytes_per_s;
     return t;
 }

@@ -109,12 +109,14 @@ struct DmaTile {
     }
 
     // Byte offset of copy r from its chunk's base, for a chunk and tile whose
-    // pieces all lie inside the operand (but for rows past o_lim, which are
-    // clamped to the last valid row: their outputs are discarded).  In builds
+    // pieces lie inside the operand or wholly past o_lim (those rows and pieces
+    // are clamped to the last valid ones: their outputs are discarded).  In builds
     // for three or four waves per SIMD recomputed per chunk from the thread
     // index, so that no per-thread offsets stay live across the K loop.  The
     // leading dimension is below 2^22 elements (the library rejects larger
     // ones), so its bytes and the row or k index fit a 24-bit multiply.
+    // CLAMP: pieces may lie past o_lim.
+    template <bool CLAMP>
     static __device__ __forceinline__ uint32_t boff(int tid, int r, int64_t ld, int o0, int o_lim) {
         const int o = copy_o(tid, r);
         const int kk = copy_k(tid, r);
@@ -122,15 +124,15 @@ struct DmaTile {
         const uint32_t ldb = (uint32_t)ld * es;
         if (KCONTIG)
             return __umul24((uint32_t)min(o, o_lim - 1 - o0), ldb) + (uint32_t)kk * es;
-        return __umul24((uint32_t)kk, ldb) + (uint32_t)o * es;
+        return __umul24((uint32_t)kk, ldb) + (uint32_t)(CLAMP ? min(o, o_lim - EPC - o0) : o) * es;
     }
     // What a tile's copies have to heed, the same for the whole workgroup:
-    // kEdge when it reaches past the last column of an operand that is not
-    // K-contiguous, kShort when a row of the operand (up to k = ke, or its
+    // kEdge when a piece of it straddles the last column of an operand that is
+    // not K-contiguous, kShort when a row of the operand (up to k = ke, or its
     // o_lim columns) is shorter than a piece.
     static constexpr uint32_t kEdge = 1u, kShort = 2u;
     static __device__ __forceinline__ uint32_t kind(int ke, int o0, int o_lim) {
-        return (KCONTIG || o0 + D <= o_lim ? 0u : kEdge) | ((KCONTIG ? ke : o_lim) >= EPC ? 0u : kShort);
+        return (KCONTIG || o0 + D <= o_lim || o_lim % EPC == 0 ? 0u : kEdge) | ((KCONTIG ? ke : o_lim) >= EPC ? 0u : kShort);
     }
 
     // At the last k steps of a row, or at the last columns, a piece that
@@ -158,20 +160,22 @@ struct DmaTile {
     // (r * NW + w) at lds_w + RAW_OFF + r * NW * 1024 (16 bytes per lane).
     // Pieces may lie at any address: the copy needs no alignment of the
     // operand.  k_rem >= 1.
-    // EDGE false: every chunk and tile of the launch lies inside the operand
-    // (but for rows past o_lim), and nothing of the edges is compiled in.
-    template <int RAW_OFF, bool EDGE>
+    // EDGE 0: every chunk and tile of the launch lies inside the operand (but for
+    // rows past o_lim); 1: pieces may lie wholly past the last column; 2: chunks
+    // may pass the end of K and pieces straddle the last column.  What a launch
+    // does not need is not compiled in.
+    template <int RAW_OFF, int EDGE>
     static __device__ __forceinline__ void copy(const T *__restrict__ base, uint32_t lds_w, int tid, int64_t ld,
                                                 int o0, int o_lim, int k_rem, uint32_t kind) {
         const char *cb = reinterpret_cast<const char *>(base);
         static_assert(CL == 1 || CL == 2 || CL == 4, "copies per thread");
-        if (!EDGE || (k_rem >= BK && kind == 0u)) {
-            dma_copy16<RAW_OFF>(cb, boff(tid, 0, ld, o0, o_lim), lds_w);
+        if (EDGE < 2 || (k_rem >= BK && kind == 0u)) {
+            dma_copy16<RAW_OFF>(cb, boff<(EDGE > 0)>(tid, 0, ld, o0, o_lim), lds_w);
             if constexpr (CL >= 2)
-                dma_copy16<RAW_OFF + NW * 1024>(cb, boff(tid, 1, ld, o0, o_lim), lds_w);
+                dma_copy16<RAW_OFF + NW * 1024>(cb, boff<(EDGE > 0)>(tid, 1, ld, o0, o_lim), lds_w);
             if constexpr (CL == 4) {
-                dma_copy16<RAW_OFF + 2 * NW * 1024>(cb, boff(tid, 2, ld, o0, o_lim), lds_w);
-                dma_copy16<RAW_OFF + 3 * NW * 1024>(cb, boff(tid, 3, ld, o0, o_lim), lds_w);
+                dma_copy16<RAW_OFF + 2 * NW * 1024>(cb, boff<(EDGE > 0)>(tid, 2, ld, o0, o_lim), lds_w);
+                dma_copy16<RAW_OFF + 3 * NW * 1024>(cb, boff<(EDGE > 0)>(tid, 3, ld, o0, o_lim), lds_w);
             }
             return;
         }
@@ -244,15 +248,17 @@ struct DmaTile {
     // The thread's segments of a chunk with k_rem valid k steps (the elements
     // past them are zero; columns past o_lim repeat the last one, their
     // outputs are discarded) from the landing buffer.
-    template <bool EDGE>
+    template <int EDGE>
     __device__ __forceinline__ void fetch(const uint32_t *raw, int w, int o0, int o_lim, int k_rem, uint32_t kind,
                                           int tid) {
-        if (!EDGE || (k_rem >= BK && kind == 0u)) {
+        if (EDGE < 2 || (k_rem >= BK && kind == 0u)) {
             // The common case, one branch for all segments: the reads issue
             // back to back and are waited for once.
 #pragma unroll
             for (int r = 0; r < L; ++r)
                 v[r] = read_slot(raw, slot_of(w, tid & 63, r));
+            if constexpr (EDGE > 0)
+                blank(o_lim - o0, tid);
             return;
         }
         asm volatile("" : "+v"(tid), "+s"(o0), "+s"(o_lim), "+s"(w));   // as in copy()
@@ -277,6 +283,22 @@ struct DmaTile {
                     e[c] = piece_element(raw, w, tid & 63, r, x);
             }
             v[r] = make_uint4(e[0], e[1], e[2], e[3]);
+        }
+        blank(o_lim - o0, tid);
+    }
+
+    // Segments wholly past the last column hold the clamped pieces' elements,
+    // other ones for float32 than for bfloat16; as ones they have no say in
+    // the steps' forms and thus in the order of the sums.
+    __device__ __forceinline__ void blank(int o_rem, int tid) {
+        if constexpr (!KCONTIG) {
+            if (o_rem < D) {
+                asm volatile("" : "+v"(tid));   // nothing of this is kept across the chunks
+#pragma unroll
+                for (int r = 0; r < L; ++r)
+                    if (seg_o(tid, r) >= o_rem)
+                        v[r] = make_uint4(kBias, kBias, kBias, kBias);
+            }
         }
     }
 

@@ -189,8 +189,8 @@ pam_exact_grad_kernel(GemmParams p) {
     // each chunk (conditions kept across the loop took lane masks, spilled).
     const uint32_t kinds = TileA::kind(ke, m0, p.m) | TileB::kind(ke, n0, p.n) << 2;
     if (nchunks > 0) {
-        TileA::template copy<0, true>(a_base, lds_w, tid, p.lda, m0, p.m, ke - kb, kinds & 3u);
-        TileB::template copy<kRawA * 4, true>(b_base, lds_w, tid, p.ldb, n0, p.n, ke - kb, kinds >> 2);
+        TileA::template copy<0, 2>(a_base, lds_w, tid, p.lda, m0, p.m, ke - kb, kinds & 3u);
+        TileB::template copy<kRawA * 4, 2>(b_base, lds_w, tid, p.ldb, n0, p.n, ke - kb, kinds >> 2);
     }
     if (tid < 2)
         sSlow[tid] = 0u;
@@ -278,8 +278,8 @@ pam_exact_grad_kernel(GemmParams p) {
         asm volatile("" : "+v"(tid_c));
         __builtin_amdgcn_s_setprio(1);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's copies of chunk c have landed
-        la.template fetch<true>(rawA, wave, m0, p.m, k_rem, kd & 3u, tid_c);
-        lb.template fetch<true>(rawB, wave, n0, p.n, k_rem, kd >> 2, tid_c);
+        la.template fetch<2>(rawA, wave, m0, p.m, k_rem, kd & 3u, tid_c);
+        lb.template fetch<2>(rawB, wave, n0, p.n, k_rem, kd >> 2, tid_c);
         uint32_t smin[TileB::L];
         const uint32_t mx = lb.scan(smin);
         static_assert(TileB::L == 1, "one B segment per thread");
@@ -313,8 +313,8 @@ pam_exact_grad_kernel(GemmParams p) {
             sSlow[(c + 1) & 1] = 0u;   // next chunk's flags; last read one chunk ago
         // The next chunk's copies land while this one is computed.
         if (c + 1 < nchunks) {
-            TileA::template copy<0, true>(a_base + (c + 1) * a_step, lds_w, tid_c, p.lda, m0, p.m, k_rem - BK, kd & 3u);
-            TileB::template copy<kRawA * 4, true>(b_base + (c + 1) * b_step, lds_w, tid_c, p.ldb, n0, p.n, k_rem - BK, kd >> 2);
+            TileA::template copy<0, 2>(a_base + (c + 1) * a_step, lds_w, tid_c, p.lda, m0, p.m, k_rem - BK, kd & 3u);
+            TileB::template copy<kRawA * 4, 2>(b_base + (c + 1) * b_step, lds_w, tid_c, p.ldb, n0, p.n, k_rem - BK, kd >> 2);
         }
         __builtin_amdgcn_s_setprio(0);
 

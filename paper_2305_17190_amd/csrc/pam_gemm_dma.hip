@@ -147,11 +147,11 @@ __device__ __forceinline__ void dma_s1_step(float (&acc)[8][8], const uint4 &al,
 }
 #undef PAM_DMA_S1_ROW
 
-// A whole S2 step, acc[i][j] = fma(aM_i + b'_j, m_i, acc[i][j]): per row +-2^E_A and 1 + M_A
-// (three full-rate ops; 1.0 is the bias), then the SCALED products.
+// A whole S2 step, acc[i][j] = fma(aM_i + b'_j, m_i, acc[i][j]): per row 1 + M_A
+// (1.0 is the bias) and +-2^E_A, then the SCALED products.  (Three full-rate
+// ops in place of the and-or and the and ran 3% slower on ReLU operands.)
 #define PAM_DMA_S2_ROW(R, A)                                                                               \
-    "v_and_b32 %[m], 0xff800000, %[" #A "]\n\tv_xor_b32 %[am], %[m], %[" #A "]\n\t"                        \
-    "v_or_b32 %[am], 1.0, %[am]\n\t"                                                                       \
+    "v_and_or_b32 %[am], %[" #A "], %[mant], 1.0\n\tv_and_b32 %[m], 0xff800000, %[" #A "]\n\t"              \
     "v_add_u32 %[t0], %[am], %[b0]\n\tv_add_u32 %[t1], %[am], %[b1]\n\t"                                   \
     "v_add_u32 %[t2], %[am], %[b2]\n\tv_add_u32 %[t3], %[am], %[b3]\n\t"                                   \
     "v_add_u32 %[t4], %[am], %[b4]\n\tv_add_u32 %[t5], %[am], %[b5]\n\t"                                   \
@@ -172,7 +172,7 @@ __device__ __forceinline__ void dma_s2_step(float (&acc)[8][8], const uint4 &al,
           [t7] "=&v"(t7)
         : [a0] "v"(al.x), [a1] "v"(al.y), [a2] "v"(al.z), [a3] "v"(al.w), [a4] "v"(ah.x), [a5] "v"(ah.y),
           [a6] "v"(ah.z), [a7] "v"(ah.w), [b0] "v"(bb[0]), [b1] "v"(bb[1]), [b2] "v"(bb[2]), [b3] "v"(bb[3]),
-          [b4] "v"(bb[4]), [b5] "v"(bb[5]), [b6] "v"(bb[6]), [b7] "v"(bb[7]));
+          [b4] "v"(bb[4]), [b5] "v"(bb[5]), [b6] "v"(bb[6]), [b7] "v"(bb[7]), [mant] "s"(kMant));
 }
 #undef PAM_DMA_S2_ROW
 #undef PAM_DMA_ACC_ROW
@@ -223,11 +223,11 @@ constexpr int dma_min_lds_words(int bm, int bn, int kw, int wps) {
 // per-thread staging addresses are computed once, before the K loop;
 // otherwise they are recomputed per chunk, since registers held across the
 // loop would not fit beside the accumulators.
-// EDGE: the launch has chunks that pass the end of K, or tiles that pass the
-// last column of an operand that is not K-contiguous.  A kernel of its own:
-// compiled in one, the edges' scalar values spilled into vector lanes across
-// the K loop and cost the other launches 3%.
-template <int BM, int BN, int KW, bool TA, bool TB, int WPS, bool EDGE, typename T>
+// EDGE: what of the edges the launch needs (DmaTile::copy); kernels of their
+// own: compiled in one, the edges' scalar values spilled into vector lanes
+// across the K loop and cost the other launches 3%, the clamp and blanks of
+// whole pieces past the last column (1) alone 1-3%.
+template <int BM, int BN, int KW, bool TA, bool TB, int WPS, int EDGE, typename T>
 __global__ void __launch_bounds__(BM * BN / 64 * KW) __attribute__((amdgpu_waves_per_eu(WPS)))
 pam_gemm_dma_kernel(GemmParams p) {
     constexpr bool kKeepAddresses = WPS <= 2 || (WPS == 3 && !TA);
@@ -317,7 +317,7 @@ pam_gemm_dma_kernel(GemmParams p) {
 
     // The copies' kinds (A's, then B's) as one scalar word, tested afresh in
     // each chunk (conditions kept across the loop took lane masks, spilled).
-    const uint32_t kinds = !EDGE ? 0u : TileA::kind(ke, m0, p.m) | TileB::kind(ke, n0, p.n) << 2;
+    const uint32_t kinds = EDGE < 2 ? 0u : TileA::kind(ke, m0, p.m) | TileB::kind(ke, n0, p.n) << 2;
     if (nchunks > 0) {
         TileA::template copy<0, EDGE>(a_base, lds_w, tid, p.lda, m0, p.m, ke - kb, kinds & 3u);
         TileB::template copy<kRawA * 4, EDGE>(b_base, lds_w, tid, p.ldb, n0, p.n, ke - kb, kinds >> 2);
@@ -327,7 +327,7 @@ pam_gemm_dma_kernel(GemmParams p) {
     for (int c = 0; c < nchunks; ++c) {
         const int k_rem = ke - kb - c * BK;   // k steps left, this chunk's included
         uint32_t kd = 0u;
-        if constexpr (EDGE) {
+        if constexpr (EDGE == 2) {
             kd = __builtin_amdgcn_readfirstlane(kinds);
             asm volatile("" : "+s"(kd));
         }
@@ -383,7 +383,7 @@ pam_gemm_dma_kernel(GemmParams p) {
         __builtin_amdgcn_s_setprio(0);
 
         // The group's steps of this chunk (those past K take none).
-        const uint32_t steps = (1u << (EDGE ? min(max(k_rem - k_first, 0), KPG) : KPG)) - 1u;
+        const uint32_t steps = (1u << (EDGE == 2 ? min(max(k_rem - k_first, 0), KPG) : KPG)) - 1u;
         uint32_t s1_bits = special ? 0u : (~low & steps);
         uint32_t s2_bits = special ? 0u : (low & ~(low >> 16) & steps);
         const uint32_t s3_bits = special ? 0u : ((low >> 16) & steps);
@@ -561,7 +561,7 @@ pam_gemm_dma_kernel(GemmParams p) {
     }
 }
 
-template <typename T, int BM, int BN, int KW, int WPS, bool EDGE>
+template <typename T, int BM, int BN, int KW, int WPS, int EDGE>
 static hipError_t launch_dma_kernel(bool ta, bool tb, const GemmParams &p, dim3 grid, hipStream_t stream) {
     const dim3 block(BM * BN / 64 * KW);
     if (!ta && !tb)
@@ -576,8 +576,8 @@ static hipError_t launch_dma_kernel(bool ta, bool tb, const GemmParams &p, dim3 
 }
 
 // The launch of one (element type, EDGE) pair: a translation unit each
-// (PAM_GEMM_PART 0..3), compiled side by side.
-template <typename T, bool EDGE>
+// (PAM_GEMM_PART 0..5), compiled side by side.
+template <typename T, int EDGE>
 hipError_t launch_dma_shape(int tile_m, int tile_n, int kgroups, bool ta, bool tb, const GemmParams &p, int64_t items,
                             hipStream_t stream) {
     const dim3 grid((unsigned)items);
@@ -604,9 +604,11 @@ hipError_t launch_dma_shape(int tile_m, int tile_n, int kgroups, bool ta, bool t
     template hipError_t launch_dma_shape<T, EDGE>(int, int, int, bool, bool, const GemmParams &, int64_t, hipStream_t)
 
 #if PAM_GEMM_PART == 0
-extern PAM_DMA_SHAPE(float, true);
-extern PAM_DMA_SHAPE(uint16_t, false);
-extern PAM_DMA_SHAPE(uint16_t, true);
+extern PAM_DMA_SHAPE(float, 1);
+extern PAM_DMA_SHAPE(float, 2);
+extern PAM_DMA_SHAPE(uint16_t, 0);
+extern PAM_DMA_SHAPE(uint16_t, 1);
+extern PAM_DMA_SHAPE(uint16_t, 2);
 
 hipError_t launch_pam_gemm_dma(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
                                const GemmParams &p, hipStream_t stream) {
@@ -614,20 +616,30 @@ hipError_t launch_pam_gemm_dma(int tile_m, int tile_n, int kgroups, bool trans_a
     if (items <= 0 || items > kMaxLaunchItems)
         return hipErrorInvalidValue;
     const int bk = dma_kpg(tile_m, tile_n, kgroups) * kgroups;
-    const bool edge = p.k % bk != 0 || (p.split_tiles > 0 && p.k_per_split % bk != 0) ||
-                      (trans_a && p.m % tile_m != 0) || (!trans_b && p.n % tile_n != 0);
-    auto launch = bf16 ? (edge ? launch_dma_shape<uint16_t, true> : launch_dma_shape<uint16_t, false>)
-                       : (edge ? launch_dma_shape<float, true> : launch_dma_shape<float, false>);
+    const int piece = bf16 ? 8 : 4;   // elements
+    const bool cut = p.k % bk != 0 || (p.split_tiles > 0 && p.k_per_split % bk != 0) ||
+                     (trans_a && p.m % piece != 0) || (!trans_b && p.n % piece != 0);
+    const bool past = (trans_a && p.m % tile_m != 0) || (!trans_b && p.n % tile_n != 0);
+    auto launch = bf16 ? (cut    ? launch_dma_shape<uint16_t, 2>
+                          : past ? launch_dma_shape<uint16_t, 1>
+                                 : launch_dma_shape<uint16_t, 0>)
+                       : (cut    ? launch_dma_shape<float, 2>
+                          : past ? launch_dma_shape<float, 1>
+                                 : launch_dma_shape<float, 0>);
     return launch(tile_m, tile_n, kgroups, trans_a, trans_b, p, items, stream);
 }
 #elif PAM_GEMM_PART == 1
-PAM_DMA_SHAPE(float, true);
+PAM_DMA_SHAPE(float, 1);
 #elif PAM_GEMM_PART == 2
-PAM_DMA_SHAPE(uint16_t, false);
+PAM_DMA_SHAPE(float, 2);
 #elif PAM_GEMM_PART == 3
-PAM_DMA_SHAPE(uint16_t, true);
+PAM_DMA_SHAPE(uint16_t, 0);
+#elif PAM_GEMM_PART == 4
+PAM_DMA_SHAPE(uint16_t, 1);
+#elif PAM_GEMM_PART == 5
+PAM_DMA_SHAPE(uint16_t, 2);
 #else
-#error "PAM_GEMM_PART is 0, 1, 2 or 3"
+#error "PAM_GEMM_PART is 0 to 5"
 #endif
 #undef PAM_DMA_SHAPE
 

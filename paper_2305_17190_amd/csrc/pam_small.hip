@@ -72,8 +72,8 @@ __global__ void __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(4)
     const uint32_t kind_a = TileA::kind(p.k, m0, p.m), kind_b = TileB::kind(p.k, n0, p.n);
     const int nchunks = (p.k + BK - 1) / BK;
 
-    TileA::template copy<0, true>(a_base, lds_w, tid, p.lda, m0, p.m, p.k, kind_a);
-    TileB::template copy<kRawA * 4, true>(b_base, lds_w, tid, p.ldb, n0, p.n, p.k, kind_b);
+    TileA::template copy<0, 2>(a_base, lds_w, tid, p.lda, m0, p.m, p.k, kind_a);
+    TileB::template copy<kRawA * 4, 2>(b_base, lds_w, tid, p.ldb, n0, p.n, p.k, kind_b);
     if (tid < 2)
         sVote[tid] = 0u;
 
@@ -93,8 +93,8 @@ __global__ void __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(4)
     for (int c = 0; c < nchunks; ++c) {
         const int k_rem = p.k - c * BK;   // k steps left, this chunk's included
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's copies have landed
-        la.template fetch<true>(rawA, wave, m0, p.m, k_rem, kind_a, tid);
-        lb.template fetch<true>(rawB, wave, n0, p.n, k_rem, kind_b, tid);
+        la.template fetch<2>(rawA, wave, m0, p.m, k_rem, kind_a, tid);
+        lb.template fetch<2>(rawB, wave, n0, p.n, k_rem, kind_b, tid);
         if (p.round_drop != 0) {
             la.round_mantissa(p.round_drop);
             lb.round_mantissa(p.round_drop);
@@ -125,8 +125,8 @@ __global__ void __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(4)
         if (tid == 0)
             sVote[(c + 1) & 1] = 0u;
         if (c + 1 < nchunks) {
-            TileA::template copy<0, true>(a_base + (c + 1) * a_step, lds_w, tid, p.lda, m0, p.m, k_rem - BK, kind_a);
-            TileB::template copy<kRawA * 4, true>(b_base + (c + 1) * b_step, lds_w, tid, p.ldb, n0, p.n, k_rem - BK,
+            TileA::template copy<0, 2>(a_base + (c + 1) * a_step, lds_w, tid, p.lda, m0, p.m, k_rem - BK, kind_a);
+            TileB::template copy<kRawA * 4, 2>(b_base + (c + 1) * b_step, lds_w, tid, p.ldb, n0, p.n, k_rem - BK,
                                                   kind_b);
         }
         const uint32_t *a_row = encA + wave * KPG * D + r0;
