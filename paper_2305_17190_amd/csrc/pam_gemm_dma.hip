@@ -74,6 +74,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "pam_dma_tile.h"
 #include "pam_internal.h"
 #include "pam_scalar.h"
@@ -324,10 +326,11 @@ pam_gemm_dma_kernel(GemmParams p) {
     }
 
     const int k_first = grp * KPG;
-    for (int c = 0; c < nchunks; ++c) {
+    auto chunk = [&](auto edge, int c) {
+        constexpr int E = decltype(edge)::value;   // of this chunk and the next
         const int k_rem = ke - kb - c * BK;   // k steps left, this chunk's included
         uint32_t kd = 0u;
-        if constexpr (EDGE == 2) {
+        if constexpr (E == 2) {
             kd = __builtin_amdgcn_readfirstlane(kinds);
             asm volatile("" : "+s"(kd));
         }
@@ -341,8 +344,8 @@ pam_gemm_dma_kernel(GemmParams p) {
         // This thread's copies of chunk c have landed (the only vector-memory
         // operations outstanding).
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        la.template fetch<EDGE>(rawA, wave, m0, p.m, k_rem, kd & 3u, tid_c);
-        lb.template fetch<EDGE>(rawB, wave, n0, p.n, k_rem, kd >> 2, tid_c);
+        la.template fetch<E>(rawA, wave, m0, p.m, k_rem, kd & 3u, tid_c);
+        lb.template fetch<E>(rawB, wave, n0, p.n, k_rem, kd >> 2, tid_c);
 
         if (p.round_drop != 0) {
             la.round_mantissa(p.round_drop);
@@ -376,14 +379,14 @@ pam_gemm_dma_kernel(GemmParams p) {
         // The next chunk's copies land while this one is computed (the
         // landing slots are this thread's own and were read above).
         if (c + 1 < nchunks) {
-            TileA::template copy<0, EDGE>(a_base + (c + 1) * a_step, lds_w, tid_c, p.lda, m0, p.m, k_rem - BK, kd & 3u);
-            TileB::template copy<kRawA * 4, EDGE>(b_base + (c + 1) * b_step, lds_w, tid_c, p.ldb, n0, p.n, k_rem - BK, kd >> 2);
+            TileA::template copy<0, E>(a_base + (c + 1) * a_step, lds_w, tid_c, p.lda, m0, p.m, k_rem - BK, kd & 3u);
+            TileB::template copy<kRawA * 4, E>(b_base + (c + 1) * b_step, lds_w, tid_c, p.ldb, n0, p.n, k_rem - BK, kd >> 2);
         }
 
         __builtin_amdgcn_s_setprio(0);
 
         // The group's steps of this chunk (those past K take none).
-        const uint32_t steps = (1u << (EDGE == 2 ? min(max(k_rem - k_first, 0), KPG) : KPG)) - 1u;
+        const uint32_t steps = (1u << (E == 2 ? min(max(k_rem - k_first, 0), KPG) : KPG)) - 1u;
         uint32_t s1_bits = special ? 0u : (~low & steps);
         uint32_t s2_bits = special ? 0u : (low & ~(low >> 16) & steps);
         const uint32_t s3_bits = special ? 0u : ((low >> 16) & steps);
@@ -465,6 +468,17 @@ pam_gemm_dma_kernel(GemmParams p) {
                     acc[i][j] += __uint_as_float(pam_full(aa[i], bb[j] + kBias));
             }
         }
+    };
+    // In a launch with cut chunks the others run a loop without their code
+    // (1250 x 7870 x 6276 2344 -> 2246 us, 768 x 192 x 12601 95.8 -> 92.6 us).
+    constexpr int kInner = EDGE < 2 ? EDGE : 1;
+    const int inner = EDGE < 2 || (ke - kb) % BK == 0 ? nchunks : max(nchunks - 2, 0);
+    const int first = kinds != 0u ? 0 : inner;
+    for (int c = 0; c < first; ++c)
+        chunk(std::integral_constant<int, kInner>{}, c);
+    if constexpr (EDGE == 2) {
+        for (int c = first; c < nchunks; ++c)
+            chunk(std::integral_constant<int, 2>{}, c);
     }
 
     // Epilogue: the output tile in C, or this K slice's partial tile (packed,
