@@ -101,8 +101,8 @@ constexpr int64_t kMaxHybridTiles = 1 << 20;
 constexpr int64_t kOneRoundHybridMinK = 512;
 // Most 32 x 32 tiles of a small product (small_product).
 constexpr int64_t kMaxSmallTiles = 2048;
-// Shortest K for which a launch is taken to last at least one whole-K tile
-// (plan_time).
+// Shortest K for which a hybrid launch is taken to last at least one whole-K
+// tile (choose_plan).
 constexpr int64_t kWholeTileBoundMinK = 2048;
 // Split counts the plan search considers.
 constexpr int kSplitChoices[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48, 56, 64};
@@ -168,13 +168,6 @@ double plan_time(const Shape &c, const Plan &p, int64_t m, int64_t n, int64_t k,
     const double wg_slice = per_chunk * double(ceil_div(p.k_per_split, bk)) + costs.workgroup_s;
     const int64_t displaced = rem > 0 ? (int64_t)std::ceil(double(rem) * wg_whole / wg_slice) : 0;
     double t = double(before) * wg_whole + rounds_time(c, split_tiles * p.splits + displaced, wg_slice, before);
-    // A whole-K tile is not divisible: where all of them start at once beside
-    // slices, one bounds the launch (1536 x 3264 x 16238 ran 6.9 ms with 56
-    // whole tiles of 312, 3.7 ms with all of them split).  For long K only:
-    // a short whole tile beside few others runs up to twice as fast as in a
-    // full compute unit, and the plans without the bound measured well there.
-    if (whole > 0 && before == 0 && k >= kWholeTileBoundMinK)
-        t = std::max(t, wg_whole);
     t += costs.split_s + double(p.splits + 1) * double(split_tiles) * c.bm * c.bn * 4.0 / costs.partial_bytes_per_s;
     return t;
 }
@@ -280,6 +273,32 @@ Plan choose_plan(int64_t m, int64_t n, int64_t k, int64_t batch, size_t max_ws_b
                 if (!seen && tails[i] > 0 && tails[i] < tiles)
                     consider(c, make_plan(c, k, s, tiles - tails[i]));
             }
+        }
+    }
+    // A whole-K tile is not divisible: where all of them start at once beside
+    // slices, one bounds the launch (1536 x 3264 x 16238 ran 6.9 ms with 56 whole
+    // tiles of 312, 3.7 ms with all of them split; 2880 x 1416 x 4048 2.0 and 0.8
+    // ms).  Every tile is then split, into at least so many slices that the
+    // mean length of a sum, and with it the rounding error, is no larger than
+    // the hybrid's.  For long K only: a short whole tile beside few others runs
+    // up to twice as fast as in a full compute unit, and the hybrids measured
+    // well there.
+    if (have[1] && best[1].whole_tiles > 0 && k >= kWholeTileBoundMinK) {
+        const Plan hybrid = best[1];
+        for (const auto &c : kShapes) {
+            if (c.bm != hybrid.tile_m || c.bn != hybrid.tile_n || c.kw != hybrid.kgroups)
+                continue;
+            const int64_t slots = (int64_t)c.per_cu * kComputeUnits;
+            const double one = double(c.bm) * c.bn * pamk::kChunkK * slots / c.rate * double(ceil_div(k, pamk::kChunkK));
+            if (hybrid.whole_tiles >= slots || one <= best_t[1])
+                continue;
+            best_t[1] = one;
+            const double tiles = double(ceil_div(m, c.bm) * ceil_div(n, c.bn) * batch);
+            const double whole = double(hybrid.whole_tiles);
+            const double least = tiles / (whole + (tiles - whole) / hybrid.splits);
+            for (const int s : kSplitChoices)
+                if (s > 1 && s >= least && s <= std::min(kMaxSplits, k / (4 * pamk::kChunkK)))
+                    consider(c, make_plan(c, k, s));
         }
     }
     if (have[1] && best_t[1] < kSplitMargin * best_t[0])
