@@ -37,6 +37,32 @@ def test_row_counts_widths_and_k(few, wide, k, swap):
     check_gemm(tiled, c_ref, s_ref, k, "tiled")
 
 
+@pytest.mark.parametrize("few", [8, 32])
+def test_tiny_values_do_not_take_the_complete_definition(few):
+    """Tiny normals cost a rounding more per term, as in the tiled kernel, not
+    the complete definition of every term near them (which took 6 to 10 times as
+    long): at most 3 times the time of clean operands."""
+    import torch
+    note(f"skinny tiny values few={few}")
+    g = torch.Generator(device=device()).manual_seed(1260)
+    x = torch.randn((few, 4096), generator=g, device=device())
+    w = torch.randn((4096, 4096), generator=g, device=device())
+    spiced = torch.where(torch.rand(w.shape, generator=g, device=device()) < 1e-3, torch.full_like(w, 1.5e-38), w)
+    best = {}
+    for _ in range(5):
+        for name, d in (("clean", w), ("tiny", spiced)):
+            pam.gemm(x, d, trans_b=True)
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            t0.record()
+            for _ in range(20):
+                pam.gemm(x, d, trans_b=True)
+            t1.record()
+            t1.synchronize()
+            best[name] = min(best.get(name, 1e9), t0.elapsed_time(t1))
+    print(f"few={few}: {best}", flush=True)
+    assert best["tiny"] < 3.0 * best["clean"], best
+
+
 @pytest.mark.parametrize("few", [2, 7, 12])
 @pytest.mark.parametrize("bits", [23, 7, 3])
 def test_batches_strides_and_narrow_mantissas(few, bits):
