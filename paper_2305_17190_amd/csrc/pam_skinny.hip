@@ -60,29 +60,39 @@ __device__ __forceinline__ uint32_t round_bits(uint32_t u, int drop) {
     return (u & kExpMask) == kExpMask ? u : r;
 }
 
-// Four consecutive elements of a row from element k, at any address, as
-// float32 encodings; elements past the row's end are zero.
-__device__ __forceinline__ void load4(const float *row, int k, int n, uint32_t (&e)[4]) {
+// Four consecutive elements of a row from element k, at any address, as they
+// are in memory; elements past the row's end are zero.  Nothing is computed from
+// them here, so that a load stays in flight until its chunk is used: bfloat16
+// elements, widened as they were loaded, were waited for at once (8 x 4096 x 4096
+// took 28.8 us, now 15.9 us).
+__device__ __forceinline__ void load4(const float *row, int k, int n, uint32_t (&w)[4]) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
     if (k + 4 <= n) {
         const u32x4 x = *reinterpret_cast<const u32x4 *>(row + k);
-        e[0] = x[0]; e[1] = x[1]; e[2] = x[2]; e[3] = x[3];
+        w[0] = x[0]; w[1] = x[1]; w[2] = x[2]; w[3] = x[3];
     } else {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            e[c] = k + c < n ? __float_as_uint(row[k + c]) : 0u;
+            w[c] = k + c < n ? __float_as_uint(row[k + c]) : 0u;
     }
 }
-__device__ __forceinline__ void load4(const uint16_t *row, int k, int n, uint32_t (&e)[4]) {
+__device__ __forceinline__ void load4(const uint16_t *row, int k, int n, uint32_t (&w)[2]) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(2)));
     if (k + 4 <= n) {
         const u32x2 x = *reinterpret_cast<const u32x2 *>(row + k);
-        e[0] = x[0] << 16; e[1] = x[0] & 0xFFFF0000u; e[2] = x[1] << 16; e[3] = x[1] & 0xFFFF0000u;
+        w[0] = x[0]; w[1] = x[1];
     } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            e[c] = k + c < n ? (uint32_t)row[k + c] << 16 : 0u;
+        for (int c = 0; c < 4; c += 2)
+            w[c / 2] = (k + c < n ? (uint32_t)row[k + c] : 0u) | (k + c + 1 < n ? (uint32_t)row[k + c + 1] << 16 : 0u);
     }
+}
+// The elements as float32 encodings.
+__device__ __forceinline__ void widen4(const uint32_t (&w)[4], uint32_t (&e)[4]) {
+    e[0] = w[0]; e[1] = w[1]; e[2] = w[2]; e[3] = w[3];
+}
+__device__ __forceinline__ void widen4(const uint32_t (&w)[2], uint32_t (&e)[4]) {
+    e[0] = w[0] << 16; e[1] = w[0] & 0xFFFF0000u; e[2] = w[1] << 16; e[3] = w[1] & 0xFFFF0000u;
 }
 
 // Running bounds of the operands' magnitudes: the least nonzero one less one
@@ -145,21 +155,27 @@ __global__ void __launch_bounds__(64 * kWaves) pam_skinny_kernel(SkinnyParams p)
         for (int j = 0; j < kJ; ++j)
             acc[i][j] = 0.0f;
 
-    uint32_t wn[kJ][4], xn[XQ][4];   // the next chunk's elements
+    uint32_t wr[kJ][sizeof(T)], xr[XQ][sizeof(T)];   // the next chunk's elements
     auto fetch = [&](int k0) {
 #pragma unroll
         for (int j = 0; j < kJ; ++j)
-            load4(wrow[j], k0 + kq * 4, n, wn[j]);
+            load4(wrow[j], k0 + kq * 4, n, wr[j]);
 #pragma unroll
         for (int i = 0; i < XQ; ++i)
-            load4(xrow[i], k0 + kq * 4, n, xn[i]);
+            load4(xrow[i], k0 + kq * 4, n, xr[i]);
     };
     const int step = kStep * kwaves;
     if (kw * kStep < n)
         fetch(kw * kStep);
 #pragma unroll 1
     for (int k0 = kw * kStep; k0 < n; k0 += step) {
-        uint32_t wc[kJ][4];
+        uint32_t wn[kJ][4], xn[XQ][4], wc[kJ][4];
+#pragma unroll
+        for (int j = 0; j < kJ; ++j)
+            widen4(wr[j], wn[j]);
+#pragma unroll
+        for (int i = 0; i < XQ; ++i)
+            widen4(xr[i], xn[i]);
         Range range;
         if (p.round_drop != 0) {
 #pragma unroll

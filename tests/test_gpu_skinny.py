@@ -37,6 +37,24 @@ def test_row_counts_widths_and_k(few, wide, k, swap):
     check_gemm(tiled, c_ref, s_ref, k, "tiled")
 
 
+def best_times(products):
+    """Least time of 20 calls of each of the products, in turn."""
+    import torch
+    best = {}
+    for _ in range(5):
+        for name, (x, w) in products.items():
+            pam.gemm(x, w, trans_b=True)
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            t0.record()
+            for _ in range(20):
+                pam.gemm(x, w, trans_b=True)
+            t1.record()
+            t1.synchronize()
+            best[name] = min(best.get(name, 1e9), t0.elapsed_time(t1))
+    print(best, flush=True)
+    return best
+
+
 @pytest.mark.parametrize("few", [8, 32])
 def test_tiny_values_do_not_take_the_complete_definition(few):
     """Tiny normals cost a rounding more per term, as in the tiled kernel, not
@@ -48,19 +66,20 @@ def test_tiny_values_do_not_take_the_complete_definition(few):
     x = torch.randn((few, 4096), generator=g, device=device())
     w = torch.randn((4096, 4096), generator=g, device=device())
     spiced = torch.where(torch.rand(w.shape, generator=g, device=device()) < 1e-3, torch.full_like(w, 1.5e-38), w)
-    best = {}
-    for _ in range(5):
-        for name, d in (("clean", w), ("tiny", spiced)):
-            pam.gemm(x, d, trans_b=True)
-            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            t0.record()
-            for _ in range(20):
-                pam.gemm(x, d, trans_b=True)
-            t1.record()
-            t1.synchronize()
-            best[name] = min(best.get(name, 1e9), t0.elapsed_time(t1))
-    print(f"few={few}: {best}", flush=True)
+    best = best_times({"clean": (x, w), "tiny": (x, spiced)})
     assert best["tiny"] < 3.0 * best["clean"], best
+
+
+@pytest.mark.parametrize("few", [8, 16])
+def test_bf16_takes_no_longer_than_float32(few):
+    """bfloat16 weights are half the bytes and the same work: not 1.25 times the
+    time of float32 ones (1.5 times when their loads were waited for at once)."""
+    import torch
+    note(f"skinny bf16 time few={few}")
+    g = torch.Generator(device=device()).manual_seed(1270)
+    x, w = (torch.randn((r, 4096), generator=g, device=device()).to(torch.bfloat16) for r in (few, 4096))
+    best = best_times({"bf16": (x, w), "float32": (x.float(), w.float())})
+    assert best["bf16"] < 1.25 * best["float32"], best
 
 
 @pytest.mark.parametrize("few", [2, 7, 12])
