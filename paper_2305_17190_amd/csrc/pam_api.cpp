@@ -419,12 +419,39 @@ bool same_plan(const Plan &a, const Plan &b) {
            a.whole_tiles == b.whole_tiles;
 }
 
+// The plan's estimated time (its tile shape is one of kShapes).
+double plan_seconds(const Plan &plan, int64_t m, int64_t n, int64_t k, int64_t batch) {
+    for (const auto &c : kShapes)
+        if (c.bm == plan.tile_m && c.bn == plan.tile_n && c.kw == plan.kgroups)
+            return plan_time(c, plan, m, n, k, batch);
+    return 0.0;
+}
+
 // Products that the skinny kernel takes in place of their plan: few rows of
-// op(A) or columns of op(B), both operands K-contiguous.
-bool skinny_product(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t batch) {
+// op(A) or columns of op(B), both operands K-contiguous, where its time is
+// below the plan's estimate (by 0.85: the estimates of split plans on few tiles
+// run about 15% high).  Its time, fitted to 2500 random products: a workgroup
+// alone on its compute unit takes `first` and `alone` a chunk of 64 k steps per
+// wave, a full chip `fixed` and `full` per 256 workgroups.  What the rule
+// leaves to the plan, and why: K in a few workgroups (32 x 512 x 65536 287 us,
+// its plan's K slices 105 us), matrices of less than a workgroup's rows by the
+// thousand (2048 of 32 x 32 x 32 105 us against 17 us), 17 to 32 rows against
+// so many that the second pass costs more than the padding saves (32 x 32768 x
+// 1024 125 us against 92 us).
+bool skinny_product(pam_op_t ta, pam_op_t tb, const Plan &plan, int64_t m, int64_t n, int64_t k, int64_t batch) {
     if (ta != PAM_OP_N || tb != PAM_OP_T || std::min(m, n) > pamk::kSkinnyRows)
         return false;
-    return batch <= pamk::kMaxSkinnyItems / (ceil_div(std::max(m, n), 16) * 8);
+    if (batch > pamk::kMaxSkinnyItems / (ceil_div(std::max(m, n), 16) * 8))
+        return false;
+    struct Cost {
+        double first, alone, fixed, full;   // microseconds
+    };
+    const pamk::SkinnyShape s = pamk::skinny_shape(std::min(m, n), std::max(m, n), k);
+    const Cost c = s.rows == 4 ? Cost{2.8, 0.87, 1.0, 1.45} : s.rows == 8 ? Cost{3.1, 1.3, 1.6, 1.8} : Cost{3.7, 2.1, 2.5, 2.8};
+    const double chunks = double(ceil_div(k, pamk::kSkinnyStep * s.kwaves)) + (k % pamk::kSkinnyStep != 0 ? 0.25 : 0.0);
+    const double groups = double(s.d_tiles) * double(s.s_tiles) * double(batch) / kComputeUnits;
+    const double us = std::max(c.first + c.alone * chunks, groups * (c.fixed + c.full * chunks));
+    return us * 1e-6 < 0.85 * plan_seconds(plan, m, n, k, batch);
 }
 
 // Products that the small-product kernel takes in place of their plan: when
@@ -488,11 +515,11 @@ pam_status_t run_gemm(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t k,
     p.splits = (int32_t)L.splits;
     float *ws = L.ws_bytes > 0 ? static_cast<float *>(ext->ptr) : nullptr;
 
-    if (!forced_plan && skinny_product(ta, tb, m, n, batch)) {
+    if (!forced_plan && skinny_product(ta, tb, plan, m, n, k, batch)) {
         p.A = A;
         p.B = B;
         p.C = C;
-        const hipError_t e = pamk::launch_pam_skinny(m <= pamk::kSkinnyRows, bf16, p, batch, stream);
+        const hipError_t e = pamk::launch_pam_skinny(m <= n, bf16, p, batch, stream);
         return e == hipSuccess ? PAM_SUCCESS : fail_hip(e, "skinny product kernel launch");
     }
     if (!forced_plan && small_product(plan, m, n, k, batch)) {

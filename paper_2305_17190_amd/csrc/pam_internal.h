@@ -61,6 +61,26 @@ hipError_t launch_pam_gemm(int tile_m, int tile_n, int kgroups, bool trans_a, bo
 // for the batch; takes no plan and no workspace.
 constexpr int kSkinnyRows = 32;
 constexpr int64_t kMaxSkinnyItems = 8388607;   // workgroups of 512 threads: below 2^32 threads
+// How a launch is cut: a workgroup takes `rows` of the s few rows and, `kwaves`
+// waves along K (while each keeps at least one chunk of kSkinnyStep k steps),
+// d_rows of the d others.
+constexpr int kSkinnyStep = 64;
+constexpr int kSkinnyWaves = 8;
+struct SkinnyShape {
+    int rows, kwaves, d_rows;
+    int64_t d_tiles, s_tiles;
+};
+inline SkinnyShape skinny_shape(int64_t s, int64_t d, int64_t k) {
+    SkinnyShape r{};
+    r.rows = s <= 4 ? 4 : s <= 8 ? 8 : 16;
+    r.kwaves = 1;
+    while (r.kwaves < kSkinnyWaves && (int64_t)r.kwaves * kSkinnyStep < k)
+        r.kwaves *= 2;
+    r.d_rows = 16 * (kSkinnyWaves / r.kwaves);
+    r.d_tiles = (d + r.d_rows - 1) / r.d_rows;
+    r.s_tiles = (s + r.rows - 1) / r.rows;
+    return r;
+}
 hipError_t launch_pam_skinny(bool rows, bool bf16, const GemmParams &p, int64_t batch, hipStream_t stream);
 
 // Small products (pam_small.hip): 32 x 32 tiles, kSmallWaves waves sharing each

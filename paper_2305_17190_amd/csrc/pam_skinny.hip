@@ -21,14 +21,14 @@
 // reads as 0.  It is exact while every nonzero operand has exponent field in
 // [64, 190].  A wave's chunk holding a tiny normal (field below 64) rounds each
 // product on its own (S3 there); one holding |x| >= 2^64, inf or NaN takes the
-// complete definition (as tiny normals did: with 0.1% of them among the weights 32
-// x 4096 x 4096 took 491 us, now 58 us; on clean operands 47 us).  bfloat16 operands widen to the
-// same encodings, so their product equals the float32 one bit for bit.
+// complete definition (as tiny normals did: with 0.1% of them among the weights
+// 32 x 4096 x 4096 took 491 us, now 58 us; on clean operands 47 us).  bfloat16
+// operands widen to the same encodings, so their product equals the float32 one
+// bit for bit.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
 #include <type_traits>
 
 #include "pam_internal.h"
@@ -39,8 +39,10 @@ namespace {
 
 constexpr int kJ = 4;            // wide rows per lane
 constexpr int kWaveRows = 4 * kJ;   // wide rows per wave: lane / 16 picks four groups of kJ
-constexpr int kWaves = 8;        // waves per workgroup
-constexpr int kStep = 64;        // k per chunk: 16 lanes of four
+constexpr int kWaves = kSkinnyWaves;   // waves per workgroup
+constexpr int kStep = kSkinnyStep;     // k per chunk: 16 lanes of four
+constexpr int kFoldChunks = 32;        // a lane's longest sum: 128 terms (long K)
+static_assert(kStep == 64 && kWaveRows == 16, "skinny_shape's cut");
 
 struct SkinnyParams {
     const void *X;   // skinny operand, s rows
@@ -155,6 +157,29 @@ __global__ void __launch_bounds__(64 * kWaves) pam_skinny_kernel(SkinnyParams p)
         for (int j = 0; j < kJ; ++j)
             acc[i][j] = 0.0f;
 
+    // The lanes' sums so far, added over the 16 lanes of a row group (the result
+    // in all of them), to the running outputs: lane kq = i holds row i's.
+    static_assert(S <= 16, "one lane per row");
+    float mineacc[kJ] = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto fold = [&]() {
+        float row[kJ];
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+            for (int j = 0; j < kJ; ++j) {
+                float v = acc[i][j];
+                v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x128, 0xF, 0xF, true));
+                v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x124, 0xF, 0xF, true));
+                v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x122, 0xF, 0xF, true));
+                v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x121, 0xF, 0xF, true));
+                row[j] = i == 0 || kq == i ? v : row[j];
+                acc[i][j] = 0.0f;
+            }
+#pragma unroll
+        for (int j = 0; j < kJ; ++j)
+            mineacc[j] += row[j];
+    };
+
     uint32_t wr[kJ][sizeof(T)], xr[XQ][sizeof(T)];   // the next chunk's elements
     auto fetch = [&](int k0) {
 #pragma unroll
@@ -168,125 +193,106 @@ __global__ void __launch_bounds__(64 * kWaves) pam_skinny_kernel(SkinnyParams p)
     if (kw * kStep < n)
         fetch(kw * kStep);
 #pragma unroll 1
-    for (int k0 = kw * kStep; k0 < n; k0 += step) {
-        uint32_t wn[kJ][4], xn[XQ][4], wc[kJ][4];
+    for (int kf = kw * kStep; kf < n; kf += kFoldChunks * step) {
+        const int kend = n - kf > kFoldChunks * step ? kf + kFoldChunks * step : n;
+#pragma unroll 1
+        for (int k0 = kf; k0 < kend; k0 += step) {
+            uint32_t wn[kJ][4], xn[XQ][4], wc[kJ][4];
 #pragma unroll
-        for (int j = 0; j < kJ; ++j)
-            widen4(wr[j], wn[j]);
+            for (int j = 0; j < kJ; ++j)
+                widen4(wr[j], wn[j]);
 #pragma unroll
-        for (int i = 0; i < XQ; ++i)
-            widen4(xr[i], xn[i]);
-        Range range;
-        if (p.round_drop != 0) {
+            for (int i = 0; i < XQ; ++i)
+                widen4(xr[i], xn[i]);
+            Range range;
+            if (p.round_drop != 0) {
+#pragma unroll
+                for (int j = 0; j < kJ; ++j)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        wn[j][c] = round_bits(wn[j][c], p.round_drop);
+#pragma unroll
+                for (int i = 0; i < XQ; ++i)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        xn[i][c] = round_bits(xn[i][c], p.round_drop);
+            }
 #pragma unroll
             for (int j = 0; j < kJ; ++j)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    wn[j][c] = round_bits(wn[j][c], p.round_drop);
-#pragma unroll
-            for (int i = 0; i < XQ; ++i)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    xn[i][c] = round_bits(xn[i][c], p.round_drop);
-        }
-#pragma unroll
-        for (int j = 0; j < kJ; ++j)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                range.add(wn[j][c]);
-                // A denormal to its signed zero, then less one bias.
-                asm("v_mul_f32 %0, 1.0, %1" : "=v"(wc[j][c]) : "v"(wn[j][c]));
-                wc[j][c] -= kBias;
-            }
-#pragma unroll
-        for (int i = 0; i < XQ; ++i) {
-            uint4 am, m;
-            am.x = (xn[i][0] & kMant) | kBias; m.x = xn[i][0] & kSignExp;
-            am.y = (xn[i][1] & kMant) | kBias; m.y = xn[i][1] & kSignExp;
-            am.z = (xn[i][2] & kMant) | kBias; m.z = xn[i][2] & kSignExp;
-            am.w = (xn[i][3] & kMant) | kBias; m.w = xn[i][3] & kSignExp;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                range.add(xn[i][c]);
-            const int row = dr + 4 * i;
-            if (S % 4 == 0 || row < S) {
-                *reinterpret_cast<uint4 *>(mine + row * kStep + kq * 4) = am;
-                *reinterpret_cast<uint4 *>(mine + (S + row) * kStep + kq * 4) = m;
-            }
-        }
-        if (k0 + step < n)
-            fetch(k0 + step);
-        const bool wild = __builtin_amdgcn_ballot_w64(range.wild()) != 0u;
-        const bool tiny = __builtin_amdgcn_ballot_w64(range.tiny()) != 0u;
-        // The wave's own writes, read by its other lanes: LDS operations of a
-        // wave complete in order, and the compiler keeps them in order here.
-        asm volatile("" ::: "memory");
-        auto terms = [&](auto own) {
-            constexpr bool kOwn = decltype(own)::value;   // each product rounded on its own
-#pragma unroll
-            for (int i = 0; i < S; ++i) {
-                const uint4 am = *reinterpret_cast<const uint4 *>(mine + i * kStep + kq * 4);
-                const uint4 m = *reinterpret_cast<const uint4 *>(mine + (S + i) * kStep + kq * 4);
-                const uint32_t a4[4] = {am.x, am.y, am.z, am.w}, m4[4] = {m.x, m.y, m.z, m.w};
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-#pragma unroll
-                    for (int j = 0; j < kJ; ++j) {
-                        if constexpr (kOwn) {
-                            float t;   // in asm: the compiler would fuse the product and the sum
-                            asm("v_mul_f32 %0, %1, %2" : "=v"(t) : "v"(a4[c] + wc[j][c]), "v"(m4[c]));
-                            acc[i][j] += t;
-                        } else {
-                            acc[i][j] = __builtin_fmaf(__uint_as_float(a4[c] + wc[j][c]), __uint_as_float(m4[c]),
-                                                       acc[i][j]);
-                        }
-                    }
-            }
-        };
-        if (!wild && !tiny) {
-            terms(std::false_type{});
-        } else if (!wild) {
-            terms(std::true_type{});
-        } else {
-#pragma unroll
-            for (int i = 0; i < S; ++i) {
-#pragma unroll 1
                 for (int c = 0; c < 4; ++c) {
-                    const uint32_t xe = (mine[i * kStep + kq * 4 + c] & kMant) | mine[(S + i) * kStep + kq * 4 + c];
+                    range.add(wn[j][c]);
+                    // A denormal to its signed zero, then less one bias.
+                    asm("v_mul_f32 %0, 1.0, %1" : "=v"(wc[j][c]) : "v"(wn[j][c]));
+                    wc[j][c] -= kBias;
+                }
 #pragma unroll
-                    for (int j = 0; j < kJ; ++j) {
-                        const uint32_t we = c == 0 ? wc[j][0] : c == 1 ? wc[j][1] : c == 2 ? wc[j][2] : wc[j][3];
-                        acc[i][j] += __uint_as_float(pam_full(xe, we + kBias));
+            for (int i = 0; i < XQ; ++i) {
+                uint4 am, m;
+                am.x = (xn[i][0] & kMant) | kBias; m.x = xn[i][0] & kSignExp;
+                am.y = (xn[i][1] & kMant) | kBias; m.y = xn[i][1] & kSignExp;
+                am.z = (xn[i][2] & kMant) | kBias; m.z = xn[i][2] & kSignExp;
+                am.w = (xn[i][3] & kMant) | kBias; m.w = xn[i][3] & kSignExp;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    range.add(xn[i][c]);
+                const int row = dr + 4 * i;
+                if (S % 4 == 0 || row < S) {
+                    *reinterpret_cast<uint4 *>(mine + row * kStep + kq * 4) = am;
+                    *reinterpret_cast<uint4 *>(mine + (S + row) * kStep + kq * 4) = m;
+                }
+            }
+            if (k0 + step < n)
+                fetch(k0 + step);
+            const bool wild = __builtin_amdgcn_ballot_w64(range.wild()) != 0u;
+            const bool tiny = __builtin_amdgcn_ballot_w64(range.tiny()) != 0u;
+            // The wave's own writes, read by its other lanes: LDS operations of a
+            // wave complete in order, and the compiler keeps them in order here.
+            asm volatile("" ::: "memory");
+            auto terms = [&](auto own) {
+                constexpr bool kOwn = decltype(own)::value;   // each product rounded on its own
+#pragma unroll
+                for (int i = 0; i < S; ++i) {
+                    const uint4 am = *reinterpret_cast<const uint4 *>(mine + i * kStep + kq * 4);
+                    const uint4 m = *reinterpret_cast<const uint4 *>(mine + (S + i) * kStep + kq * 4);
+                    const uint32_t a4[4] = {am.x, am.y, am.z, am.w}, m4[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+#pragma unroll
+                        for (int j = 0; j < kJ; ++j) {
+                            if constexpr (kOwn) {
+                                float t;   // in asm: the compiler would fuse the product and the sum
+                                asm("v_mul_f32 %0, %1, %2" : "=v"(t) : "v"(a4[c] + wc[j][c]), "v"(m4[c]));
+                                acc[i][j] += t;
+                            } else {
+                                acc[i][j] = __builtin_fmaf(__uint_as_float(a4[c] + wc[j][c]), __uint_as_float(m4[c]),
+                                                           acc[i][j]);
+                            }
+                        }
+                }
+            };
+            if (!wild && !tiny) {
+                terms(std::false_type{});
+            } else if (!wild) {
+                terms(std::true_type{});
+            } else {
+#pragma unroll
+                for (int i = 0; i < S; ++i) {
+#pragma unroll 1
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t xe = (mine[i * kStep + kq * 4 + c] & kMant) | mine[(S + i) * kStep + kq * 4 + c];
+#pragma unroll
+                        for (int j = 0; j < kJ; ++j) {
+                            const uint32_t we = c == 0 ? wc[j][0] : c == 1 ? wc[j][1] : c == 2 ? wc[j][2] : wc[j][3];
+                            acc[i][j] += __uint_as_float(pam_full(xe, we + kBias));
+                        }
                     }
                 }
             }
+            asm volatile("" ::: "memory");
         }
-        asm volatile("" ::: "memory");
+        fold();
     }
-
-    // Sum over the 16 lanes of a row group (the result in all of them); lane
-    // kq = i % 16 then holds row i's outputs.
-#pragma unroll
-    for (int i = 0; i < S; ++i)
-#pragma unroll
-        for (int j = 0; j < kJ; ++j) {
-            float v = acc[i][j];
-            v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x128, 0xF, 0xF, true));
-            v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x124, 0xF, 0xF, true));
-            v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x122, 0xF, 0xF, true));
-            v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x121, 0xF, 0xF, true));
-            acc[i][j] = v;
-        }
-    static_assert(S <= 16, "one lane per row");
-    float mineacc[kJ];
-#pragma unroll
-    for (int j = 0; j < kJ; ++j)
-        mineacc[j] = acc[0][j];
-#pragma unroll
-    for (int i = 1; i < S; ++i)
-#pragma unroll
-        for (int j = 0; j < kJ; ++j)
-            mineacc[j] = kq == i ? acc[i][j] : mineacc[j];
     if (kwaves > 1) {
         float *part = reinterpret_cast<float *>(smem);
         __syncthreads();   // every wave is past its chunks
@@ -334,29 +340,25 @@ hipError_t launch_pam_skinny(bool rows, bool bf16, const GemmParams &g, int64_t 
     p.strideC = g.strideC;
     p.k = g.k;
     p.round_drop = g.round_drop;
-    // Waves along K while each keeps at least one chunk.
-    p.kwaves = 1;
-    while (p.kwaves < kWaves && p.kwaves * kStep < p.k)
-        p.kwaves *= 2;
-    const int per_s = p.s <= 4 ? 4 : p.s <= 8 ? 8 : 16;
-    const int64_t d_rows = (int64_t)kWaveRows * (kWaves / p.kwaves);
-    p.d_tiles = (int32_t)((p.d + d_rows - 1) / d_rows);
-    p.s_tiles = (p.s + per_s - 1) / per_s;
+    const SkinnyShape cut = skinny_shape(p.s, p.d, p.k);
+    p.kwaves = cut.kwaves;
+    p.d_tiles = (int32_t)cut.d_tiles;
+    p.s_tiles = (int32_t)cut.s_tiles;
     const int64_t items = (int64_t)p.d_tiles * p.s_tiles * batch;
     if (items <= 0 || items > kMaxSkinnyItems)
         return hipErrorInvalidValue;
     const dim3 grid((unsigned)items), block(64 * kWaves);
     if (bf16) {
-        if (per_s == 4)
+        if (cut.rows == 4)
             hipLaunchKernelGGL((pam_skinny_kernel<4, uint16_t>), grid, block, 0, stream, p);
-        else if (per_s == 8)
+        else if (cut.rows == 8)
             hipLaunchKernelGGL((pam_skinny_kernel<8, uint16_t>), grid, block, 0, stream, p);
         else
             hipLaunchKernelGGL((pam_skinny_kernel<16, uint16_t>), grid, block, 0, stream, p);
     } else {
-        if (per_s == 4)
+        if (cut.rows == 4)
             hipLaunchKernelGGL((pam_skinny_kernel<4, float>), grid, block, 0, stream, p);
-        else if (per_s == 8)
+        else if (cut.rows == 8)
             hipLaunchKernelGGL((pam_skinny_kernel<8, float>), grid, block, 0, stream, p);
         else
             hipLaunchKernelGGL((pam_skinny_kernel<16, float>), grid, block, 0, stream, p);

@@ -1,0 +1,57 @@
+"""Which kernel and plan the host layer launches for a call (CPU: the launches
+are recorded, not run)."""
+import pytest
+
+import dispatch_probe as probe
+
+
+def names(launches):
+    return [x.name for x in launches]
+
+
+# ---------------------------------------------------------------------------
+# Few rows
+# ---------------------------------------------------------------------------
+
+@pytest.mark.parametrize("few,wide,k", [(8, 4096, 4096), (1, 4096, 4096), (16, 4096, 4096), (32, 768, 192),
+                                        (8, 2048, 512), (4, 16, 64), (24, 512, 1024)])
+@pytest.mark.parametrize("swap", [False, True])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_few_rows_take_their_kernel(few, wide, k, swap, bf16):
+    m, n = (wide, few) if swap else (few, wide)
+    got = probe.product(m, n, k, bf16=bf16)
+    assert names(got) == ["few rows"]
+    # the side with fewer rows is the one held in LDS, also when both are few
+    assert bool(got[0].few_rows_of_a) == (m <= n)
+
+
+@pytest.mark.parametrize("few,wide,k,batch", [
+    (32, 32, 65536, 1), (8, 64, 65536, 1), (32, 512, 65536, 1), (16, 16, 16384, 1), (3, 5, 1000000, 1),   # long K
+    (32, 32768, 1024, 1), (24, 32768, 256, 1),             # two passes over many rows
+    (32, 32, 32, 2048), (8, 64, 32, 2048), (32, 512, 64, 256)])   # many small matrices
+def test_few_rows_left_to_the_plan(few, wide, k, batch):
+    """Where the few-row kernel leaves the chip idle or works for nothing, the
+    product runs its plan (or the small-product kernel)."""
+    assert "few rows" not in names(probe.product(few, wide, k, batch))
+
+
+def parameters(function, names):
+    return [case for mark in function.pytestmark if mark.name == "parametrize" and mark.args[0] == names
+            for case in mark.args[1]]
+
+
+def test_gpu_tests_reach_the_few_row_kernel():
+    """The sizes of the kernel's GPU tests do go to it."""
+    import test_gpu_skinny
+    fews = parameters(test_gpu_skinny.test_row_counts_widths_and_k, "few")
+    wides = parameters(test_gpu_skinny.test_row_counts_widths_and_k, "wide,k")
+    assert len(fews) >= 10 and len(wides) >= 6
+    for few in fews:
+        for wide, k in wides:
+            if min(few, wide) <= 32:
+                for m, n in ((few, wide), (wide, few)):
+                    assert names(probe.product(m, n, k)) == ["few rows"], (m, n, k)
+    long_k = parameters(test_gpu_skinny.test_long_k_folds_its_sums, "few,wide,k")
+    assert len(long_k) >= 4
+    for few, wide, k in long_k:
+        assert names(probe.product(few, wide, k, workspace=False)) == ["few rows"]

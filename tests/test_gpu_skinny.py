@@ -35,6 +35,25 @@ def test_row_counts_widths_and_k(few, wide, k, swap):
     c_ref, s_ref = oracle_gemm(a.ravel(), b.ravel(), False, True, m, n, k, k, k, batches=[0])
     check_gemm(c, c_ref, s_ref, k, "skinny")
     check_gemm(tiled, c_ref, s_ref, k, "tiled")
+    if few <= 32 and k >= 515 and m * n >= 64:   # two kernels: their sums have another order
+        assert not np.array_equal(c, tiled)
+
+
+@pytest.mark.parametrize("few,wide,k", [(1, 40, 16384), (3, 35, 16385), (7, 20, 33000), (12, 17, 40000)])
+def test_long_k_folds_its_sums(few, wide, k):
+    """A lane's sum is folded into the outputs every 32 chunks of 512 k steps:
+    sums that are exact in any order equal the oracle bit for bit.  (Without a
+    workspace, so that the product's plan has no K slices to win with.)"""
+    import torch
+    note(f"skinny long K few={few} wide={wide} k={k}")
+    a, b = wl.exact_sum_values((few, k), 1250), wl.exact_sum_values((wide, k), 1251)
+    ad, bd = to_dev(a), to_dev(b)
+    c = torch.full((few, wide), float("nan"), device=device())
+    st = pam.load().pam_gemm_batched(0, 1, few, wide, k, ad.data_ptr(), k, 0, bd.data_ptr(), k, 0, c.data_ptr(), wide, 0,
+                                     1, torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    c_ref, _ = oracle_gemm(a, b, False, True, few, wide, k, k, k)
+    assert np.array_equal(c.cpu().numpy().astype(np.float64), c_ref[0])
 
 
 def best_times(products):
