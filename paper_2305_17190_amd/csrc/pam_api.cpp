@@ -455,21 +455,22 @@ bool skinny_product(pam_op_t ta, pam_op_t tb, const Plan &plan, int64_t m, int64
 }
 
 // Products that the small-product kernel takes in place of their plan: when
-// its time is well below the plan's estimate (by 0.8: the estimates of split
-// plans on few tiles run 20-30% high).  Its time, measured: 3.6 us, and per
-// 128 k steps 1.9 us up to 256 tiles of 32 x 32, then 6.7 us per 1024 of them.
+// its time is below the plan's estimate (a split plan's by 0.85: those run 10-20%
+// high on few tiles, the others 20-30% low; chunks with zeros take up to 1.3
+// times as long, those with tiny normals 1.55 times).  Its time, fitted to 800 random
+// products: up to 256 tiles of 32 x 32 (one workgroup a compute unit) 4.5 us and
+// 2.45 us per 128 k steps; beyond, 5.5 us and 3.3 us per 1024 tiles, and per 128 k
+// steps 7.4 us per 1024 tiles, at least 3.4 us.
 // Only in place of pam_gemm_plan's plan: a product whose plan its workspace
 // limits keeps that plan.
 bool small_product(const Plan &plan, int64_t m, int64_t n, int64_t k, int64_t batch) {
     const int64_t tiles = ceil_div(m, 32) * ceil_div(n, 32) * batch;
     if (tiles > kMaxSmallTiles || !same_plan(plan, choose_plan(m, n, k, batch, kAnyWorkspace)))
         return false;
-    const double chunks = double(ceil_div(k, pamk::kChunkK * pamk::kSmallWaves));
-    const double small_s = 3.6e-6 + chunks * std::max(1.9e-6, 6.7e-6 * double(tiles) / 1024.0);
-    for (const auto &c : kShapes)
-        if (c.bm == plan.tile_m && c.bn == plan.tile_n && c.kw == plan.kgroups)
-            return small_s < 0.8 * plan_time(c, plan, m, n, k, batch);
-    return false;
+    const double chunks = double(k) / (pamk::kChunkK * pamk::kSmallWaves);
+    const double many = double(tiles) / 1024.0;
+    const double us = tiles <= 256 ? 4.5 + 2.45 * chunks : 5.5 + 3.3 * many + std::max(3.4, 7.4 * many) * chunks;
+    return us * 1e-6 < (plan.splits > 1 ? 0.85 : 1.0) * plan_seconds(plan, m, n, k, batch);
 }
 
 // The product under `plan` (unless forced, skinny and small products take

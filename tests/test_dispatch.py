@@ -35,6 +35,22 @@ def test_few_rows_left_to_the_plan(few, wide, k, batch):
     assert "few rows" not in names(probe.product(few, wide, k, batch))
 
 
+# ---------------------------------------------------------------------------
+# Small products
+# ---------------------------------------------------------------------------
+
+@pytest.mark.parametrize("m,n,k,batch", [(256, 256, 256, 1), (512, 512, 256, 1), (1024, 1024, 256, 1), (128, 128, 64, 1),
+                                         (197, 64, 197, 16), (256, 256, 640, 1)])
+def test_small_products_take_their_kernel(m, n, k, batch):
+    assert names(probe.product(m, n, k, batch, tb=False)) == ["small"]
+
+
+@pytest.mark.parametrize("m,n,k,batch", [(64, 1184, 1696, 1), (96, 288, 1760, 1), (352, 192, 2816, 4),
+                                         (256, 256, 2048, 1), (2048, 1024, 256, 1), (128, 128, 4096, 1)])
+def test_long_k_small_outputs_keep_their_plan(m, n, k, batch):
+    assert names(probe.product(m, n, k, batch, ta=True, tb=False))[0] == "tiled"
+
+
 def parameters(function, names):
     return [case for mark in function.pytestmark if mark.name == "parametrize" and mark.args[0] == names
             for case in mark.args[1]]
@@ -55,3 +71,12 @@ def test_gpu_tests_reach_the_few_row_kernel():
     assert len(long_k) >= 4
     for few, wide, k in long_k:
         assert names(probe.product(few, wide, k, workspace=False)) == ["few rows"]
+
+
+def test_gpu_tests_reach_the_small_product_kernel():
+    import test_gpu_small
+    sizes = parameters(test_gpu_small.test_sizes_and_layouts, "m,n,k")
+    assert len(sizes) >= 9
+    for m, n, k in sizes + [(70, 66, 300), (64, 64, 128), (45, 77, 203), (33, 40, 5)]:
+        for ta, tb in ((False, False), (False, True), (True, False), (True, True)):
+            assert names(probe.product(m, n, k, ta=ta, tb=tb)) == ["small"], (m, n, k, ta, tb)

@@ -38,12 +38,16 @@ def test_sizes_and_layouts(m, n, k, ta, tb):
     a, b = buffers(m, n, k, ta, tb, 1400 + m + n + k)
     c_ref, s_ref, k = reference(a, b, ta, tb)
     ad, bd = to_dev(a), to_dev(b)
-    check_gemm(pam.bmm(ad, bd, trans_a=ta, trans_b=tb).cpu().numpy(), c_ref, s_ref, k, "small")
-    check_gemm(pam.bmm(ad, bd, trans_a=ta, trans_b=tb, plan=TILED).cpu().numpy(), c_ref, s_ref, k, "tiled")
+    small = pam.bmm(ad, bd, trans_a=ta, trans_b=tb)
+    tiled = pam.bmm(ad, bd, trans_a=ta, trans_b=tb, plan=TILED)
+    check_gemm(small.cpu().numpy(), c_ref, s_ref, k, "small")
+    check_gemm(tiled.cpu().numpy(), c_ref, s_ref, k, "tiled")
     # the library's own plan, forced, runs as the library does
     import torch
     own = pam.bmm(ad, bd, trans_a=ta, trans_b=tb, plan=pam.plan(m, n, k))
-    assert torch.equal(own.view(torch.int32), pam.bmm(ad, bd, trans_a=ta, trans_b=tb).view(torch.int32))
+    assert torch.equal(own.view(torch.int32), small.view(torch.int32))
+    if k > 64:   # two kernels: their sums have another order
+        assert not torch.equal(tiled.view(torch.int32), small.view(torch.int32))
 
 
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
@@ -106,3 +110,26 @@ def test_every_operand_class(kind, ta, tb):
     c_ref, s_ref, _ = reference(a, b, ta, tb)
     check_gemm(pam.bmm(to_dev(a), to_dev(b), trans_a=ta, trans_b=tb).cpu().numpy(), c_ref, s_ref, k, kind)
     check_gemm(pam.bmm(to_dev(a), to_dev(b), trans_a=ta, trans_b=tb, plan=TILED).cpu().numpy(), c_ref, s_ref, k, kind)
+
+
+def test_zeros_cost_no_more_than_their_form():
+    """Half of A exact zeros: the add + fma form and one vote of each wave, not
+    one LDS atomic of each lane to one word (which took 2.2 times as long as
+    clean operands; now 1.3 times)."""
+    import torch
+    note("small zeros time")
+    g = torch.Generator(device=device()).manual_seed(1800)
+    a, b = (torch.randn((256, 1024), generator=g, device=device()) for _ in range(2))
+    best = {}
+    for _ in range(10):
+        for name, x in (("clean", a), ("zeros", torch.relu(a))):
+            pam.gemm(x, b, trans_b=True)
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            t0.record()
+            for _ in range(30):
+                pam.gemm(x, b, trans_b=True)
+            t1.record()
+            t1.synchronize()
+            best[name] = min(best.get(name, 1e9), t0.elapsed_time(t1))
+    print(best, flush=True)
+    assert best["zeros"] < 1.7 * best["clean"], best
