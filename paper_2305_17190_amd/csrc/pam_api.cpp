@@ -104,6 +104,8 @@ constexpr int64_t kMaxSmallTiles = 2048;
 // Shortest K for which a hybrid launch is taken to last at least one whole-K
 // tile (choose_plan).
 constexpr int64_t kWholeTileBoundMinK = 2048;
+// Fewest slices of the plan that then splits every tile.
+constexpr int kWholeTileSplits = 5;
 // Split counts the plan search considers.
 constexpr int kSplitChoices[] = {1, 2, 3, 4, 5, 6, 7, 8, 12, 16, 24, 32, 48, 56, 64};
 
@@ -280,10 +282,14 @@ Plan choose_plan(int64_t m, int64_t n, int64_t k, int64_t batch, size_t max_ws_b
     // tiles of 312, 3.7 ms with all of them split; 2880 x 1416 x 4048 2.0 and 0.8
     // ms).  Every tile is then split, into at least so many slices that the
     // mean length of a sum, and with it the rounding error, is no larger than
-    // the hybrid's.  For long K only: a short whole tile beside few others runs
-    // up to twice as fast as in a full compute unit, and the hybrids measured
-    // well there.
-    if (have[1] && best[1].whole_tiles > 0 && k >= kWholeTileBoundMinK) {
+    // the hybrid's (which stays where the workspace is too small for them), and
+    // into kWholeTileSplits where that fits (6428 x 2368 x 3072, 713 of 969 tiles
+    // whole: 1.80 ms and an error of 8.4e-7, in 6 slices 1.78 ms and 4.1e-7, all
+    // whole 1.96 ms and 9.9e-7; with 372 to 512 whole tiles the hybrid is 2% faster,
+    // at up to 8%, for twice the error).  For long K only: a short whole tile
+    // beside few others runs up to twice as fast as in a full compute unit, and
+    // the hybrids measured well there.
+    if (have[1] && best[1].whole_tiles > 0 && k >= kWholeTileBoundMinK && best_t[1] < kSplitMargin * best_t[0]) {
         const Plan hybrid = best[1];
         for (const auto &c : kShapes) {
             if (c.bm != hybrid.tile_m || c.bn != hybrid.tile_n || c.kw != hybrid.kgroups)
@@ -292,13 +298,18 @@ Plan choose_plan(int64_t m, int64_t n, int64_t k, int64_t batch, size_t max_ws_b
             const double one = double(c.bm) * c.bn * pamk::kChunkK * slots / c.rate * double(ceil_div(k, pamk::kChunkK));
             if (hybrid.whole_tiles >= slots || one <= best_t[1])
                 continue;
-            best_t[1] = one;
             const double tiles = double(ceil_div(m, c.bm) * ceil_div(n, c.bn) * batch);
             const double whole = double(hybrid.whole_tiles);
             const double least = tiles / (whole + (tiles - whole) / hybrid.splits);
-            for (const int s : kSplitChoices)
-                if (s > 1 && s >= least && s <= std::min(kMaxSplits, k / (4 * pamk::kChunkK)))
-                    consider(c, make_plan(c, k, s));
+            have[1] = false;
+            for (const double fewest : {std::max(double(kWholeTileSplits), least), least}) {
+                for (const int s : kSplitChoices)
+                    if (s > 1 && s >= fewest && s <= std::min(kMaxSplits, k / (4 * pamk::kChunkK)))
+                        consider(c, make_plan(c, k, s));
+                if (have[1])
+                    break;
+            }
+            return have[1] ? best[1] : hybrid;
         }
     }
     if (have[1] && best_t[1] < kSplitMargin * best_t[0])

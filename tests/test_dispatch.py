@@ -9,6 +9,13 @@ def names(launches):
     return [x.name for x in launches]
 
 
+def mean_sum(m, n, plan, batch=1):
+    """Mean length of an output's running sums, as a share of K."""
+    tm, tn, splits, _, whole = plan
+    tiles = -(-m // tm) * -(-n // tn) * batch
+    return 1.0 if splits == 1 else (whole + (tiles - whole) / splits) / tiles
+
+
 # ---------------------------------------------------------------------------
 # Few rows
 # ---------------------------------------------------------------------------
@@ -49,6 +56,29 @@ def test_small_products_take_their_kernel(m, n, k, batch):
                                          (256, 256, 2048, 1), (2048, 1024, 256, 1), (128, 128, 4096, 1)])
 def test_long_k_small_outputs_keep_their_plan(m, n, k, batch):
     assert names(probe.product(m, n, k, batch, ta=True, tb=False))[0] == "tiled"
+
+
+# ---------------------------------------------------------------------------
+# Plans
+# ---------------------------------------------------------------------------
+
+# Sizes of almost one round of 128 x 128 tiles with long K (and two others)
+# whose former plan took most tiles over the whole K and the last 256 in slices:
+# (m, n, k) -> that plan's (tiles, whole-K tiles, slices).
+NEAR_ONE_ROUND = {(6428, 2368, 3072): (969, 713, 16), (7643, 2043, 2286): (960, 704, 12),
+                  (3005, 5230, 10146): (984, 728, 53), (6865, 2208, 3584): (972, 716, 16),
+                  (17662, 852, 2400): (966, 710, 15), (14045, 533, 3984): (550, 294, 12), (8400, 945, 2061): (528, 272, 8)}
+
+
+@pytest.mark.parametrize("size", NEAR_ONE_ROUND, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("limit", [None, 1 << 30, 256 << 20, 64 << 20])
+def test_near_one_round_sums_are_no_longer_than_the_hybrids(size, limit):
+    tiles, whole, splits = NEAR_ONE_ROUND[size]
+    m, n, k = size
+    plan = probe.plan(m, n, k, max_workspace_bytes=limit)
+    hybrid_bytes = (tiles - whole) * splits * 128 * 128 * 4
+    if limit is None or limit >= hybrid_bytes:
+        assert mean_sum(m, n, plan) <= (whole + (tiles - whole) / splits) / tiles, plan
 
 
 def parameters(function, names):
