@@ -615,6 +615,11 @@ const Costs kExactCosts = {13e-6, 3e-6, 5.5e12};
 // sums keep the rounding error of a long K down (8192 x 512 and 2048 x 512
 // outputs over K = 2048 and 8192: 3.7e-7 of the result with 4 and 16 slices,
 // 5.8e-7 with 2 and 8) and cost nothing (486 / 454 us against 560 / 463).
+// Where that asks for 64 slices, 56 may do: the reduction adds eight slices in
+// pairs, which makes up for the longer slices (768 x 192 over K = 12608: 53 slices
+// 2.88e-7 in 126 us, 61 slices 2.71e-7 in 138 us; 61 added one by one 2.94e-7).
+// Seven for eight do not (1682 x 1207 over K = 10324: 6.89e-7 with 7, 5.29e-7 with
+// the 12 taken now; 12993 x 256 over K = 3050: 3.84e-7 and 3.57e-7 with 8).
 Plan choose_exact_plan(int64_t m, int64_t n, int64_t k, bool split_ok) {
     const Shape &c = kExactShape;
     Plan best = make_plan(c, k, 1);
@@ -631,7 +636,7 @@ Plan choose_exact_plan(int64_t m, int64_t n, int64_t k, bool split_ok) {
     bool have = least == 1;
     double best_t = kSplitMargin * plan_time(c, best, m, n, k, 1, kExactCosts);
     for (const int s : kSplitChoices) {
-        if (s == 1 || 8 * s < 7 * least)
+        if (s == 1 || (s < least && s < 56))
             continue;
         if (s > most)
             break;

@@ -1,8 +1,14 @@
 """Which kernel and plan the host layer launches for a call (CPU: the launches
 are recorded, not run)."""
+import random
+
 import pytest
 
 import dispatch_probe as probe
+
+
+def log_uniform(rng, lo, hi):
+    return int(round(lo * (hi / lo) ** rng.random()))
 
 
 def names(launches):
@@ -79,6 +85,25 @@ def test_near_one_round_sums_are_no_longer_than_the_hybrids(size, limit):
     hybrid_bytes = (tiles - whole) * splits * 128 * 128 * 4
     if limit is None or limit >= hybrid_bytes:
         assert mean_sum(m, n, plan) <= (whole + (tiles - whole) / splits) / tiles, plan
+
+
+def test_exact_derivative_sums_are_short():
+    """K is cut into at least as many slices as doubling gives until tiles of
+    128 x 128 times slices reach 1024 (slices of at least four chunks); 56 stand
+    for 64, whose reduction adds eights in pairs."""
+    rng = random.Random(5)
+    sizes = [(1682, 1207, 10324), (12993, 256, 3050), (768, 192, 12608)]
+    sizes += [tuple(log_uniform(rng, 16, hi) for hi in (20000, 20000, 30000)) for _ in range(3000)]
+    for m, n, k in sizes:
+        tiles = -(-m // 128) * -(-n // 128)
+        least = 1
+        while tiles * least < 1024 and least < 64 and k // (2 * least) >= 64:
+            least *= 2
+        least = min(least, 56)
+        per = -(-(-(-k // least)) // 16) * 16
+        launch = probe.exact_grad(m, n, k)[0]
+        assert launch.name == "exact"
+        assert least == 1 or launch.splits >= -(-k // per), (m, n, k, least, launch.splits)
 
 
 def parameters(function, names):
