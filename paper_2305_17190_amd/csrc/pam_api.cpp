@@ -1057,11 +1057,19 @@ pam_status_t pam_gemm_batched_with_plan(pam_op_t transA, pam_op_t transB, int64_
         return st;
     if (m == 0 || n == 0 || batch == 0)
         return PAM_SUCCESS;
-    // A plan the library would pick itself runs as the library runs it.
+    // A plan the library would pick itself runs as the library runs it, with its
+    // K slices (a multiple of 16 steps per k-group; a plan of the caller's takes
+    // multiples of 16).
     const Plan given{plan->tile_m, plan->tile_n, plan->kgroups, plan->splits, 0, plan->whole_tiles};
-    const int64_t k1 = std::max<int64_t>(k, 1);
-    const bool forced = !same_plan(given, choose_plan(m, n, k1, batch, kAnyWorkspace)) &&
-                        !same_plan(given, choose_plan(m, n, k1, batch, 0));
+    bool forced = true;
+    for (const size_t limit : {kAnyWorkspace, (size_t)0}) {
+        const Plan own = choose_plan(m, n, std::max<int64_t>(k, 1), batch, limit);
+        if (same_plan(given, own)) {
+            p = own;
+            forced = false;
+            break;
+        }
+    }
     const Workspace ws{workspace, workspace_bytes};
     return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, p, stream, 0,
                     &ws, false, forced);

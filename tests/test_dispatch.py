@@ -106,6 +106,37 @@ def test_exact_derivative_sums_are_short():
         assert least == 1 or launch.splits >= -(-k // per), (m, n, k, least, launch.splits)
 
 
+def fields(x):
+    return (x.name, x.tile_m, x.tile_n, x.kgroups, x.splits, x.k_per_split, x.whole, x.split_tiles)
+
+
+def test_own_plan_passed_in_launches_the_same():
+    """A plan equal to the library's launches what the library launches: the
+    same kernel, tiles and K slices."""
+    rng = random.Random(6)
+    sizes = [(976, 1264, 596, 1), (1738, 538, 3079, 1), (1438, 1285, 1100, 1), (256, 256, 256, 1), (70, 70, 1000, 1)]
+    sizes += [(log_uniform(rng, 1, 5000), log_uniform(rng, 1, 5000), log_uniform(rng, 1, 20000), rng.choice([1, 1, 3, 50]))
+              for _ in range(1500)]
+    kinds = set()
+    for m, n, k, batch in sizes:
+        for workspace, limit in ((True, None), (False, 0)):
+            own = probe.plan(m, n, k, batch, max_workspace_bytes=limit)
+            auto = [fields(x) for x in probe.product(m, n, k, batch, tb=False, workspace=workspace)]
+            if limit == 0 and own == probe.plan(m, n, k, batch):
+                continue
+            assert [fields(x) for x in probe.product(m, n, k, batch, tb=False, plan=own)] == auto, (m, n, k, batch, own)
+            kinds.add((auto[0][0], own[3], own[2] > 1))
+    assert {("tiled", 2, True), ("tiled", 4, True), ("tiled", 1, True), ("small", 4, False)} <= kinds
+
+
+def test_callers_plan_runs_its_tiles():
+    """A plan that is not the library's runs the tiled kernel as given."""
+    for plan in ((64, 64, 1, 4, 1), (64, 64, 3, 4, 0), (128, 64, 1, 2, 1), (128, 128, 2, 1, 1)):
+        for m, n, k in ((256, 128, 272), (70, 66, 300), (8, 64, 4096)):
+            got = probe.product(m, n, k, plan=plan)
+            assert (got[0].name, got[0].tile_m, got[0].tile_n, got[0].kgroups) == ("tiled", plan[0], plan[1], plan[3])
+
+
 def parameters(function, names):
     return [case for mark in function.pytestmark if mark.name == "parametrize" and mark.args[0] == names
             for case in mark.args[1]]

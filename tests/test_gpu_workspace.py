@@ -25,6 +25,20 @@ SHAPES = [(768, 192, 12608, 1), (8192, 2048, 512, 1), (256, 64, 256, 16), (300, 
           (4096, 1024, 4096, 1)]
 
 
+@pytest.mark.parametrize("m,n,k", [(976, 1264, 596), (1738, 538, 3079), (1438, 1285, 1100), (300, 140, 2100)])
+def test_own_split_plan_gives_the_same_bits(m, n, k):
+    """A split plan with two or four k-groups, passed back in, takes the
+    library's own K slices (multiples of 16 steps per k-group)."""
+    import torch
+    plan = pam.plan(m, n, k)
+    note(f"own split plan m={m} n={n} k={k} plan={plan}")
+    assert plan[2] > 1 and plan[3] > 1
+    g = torch.Generator(device=device()).manual_seed(92)
+    a = torch.randn((1, m, k), generator=g, device=device())
+    b = torch.randn((1, k, n), generator=g, device=device())
+    assert torch.equal(pam.bmm(a, b, plan=plan).view(torch.int32), pam.bmm(a, b).view(torch.int32))
+
+
 def forced(a, b, m, n, k, batch, plan):
     """The product under an explicit plan (workspace from torch)."""
     c = pam.bmm(a, b, plan=plan)
