@@ -465,6 +465,10 @@ bool skinny_product(pam_op_t ta, pam_op_t tb, const Plan &plan, int64_t m, int64
     return us * 1e-6 < 0.85 * plan_seconds(plan, m, n, k, batch);
 }
 
+// Whose choice a product's plan is: the library's with any workspace
+// (pam_gemm_plan's), the library's within a limit, or the caller's own.
+enum class PlanOf { kLibrary, kLimited, kCaller };
+
 // Products that the small-product kernel takes in place of their plan: when
 // its time is below the plan's estimate (a split plan's by 0.85: those run 10-20%
 // high on few tiles, the others 20-30% low; chunks with zeros take up to 1.3
@@ -474,23 +478,25 @@ bool skinny_product(pam_op_t ta, pam_op_t tb, const Plan &plan, int64_t m, int64
 // steps 7.4 us per 1024 tiles, at least 3.4 us.
 // Only in place of pam_gemm_plan's plan: a product whose plan its workspace
 // limits keeps that plan.
-bool small_product(const Plan &plan, int64_t m, int64_t n, int64_t k, int64_t batch) {
+bool small_product(const Plan &plan, PlanOf whose, int64_t m, int64_t n, int64_t k, int64_t batch) {
     const int64_t tiles = ceil_div(m, 32) * ceil_div(n, 32) * batch;
-    if (tiles > kMaxSmallTiles || !same_plan(plan, choose_plan(m, n, k, batch, kAnyWorkspace)))
+    if (tiles > kMaxSmallTiles)
         return false;
     const double chunks = double(k) / (pamk::kChunkK * pamk::kSmallWaves);
     const double many = double(tiles) / 1024.0;
     const double us = tiles <= 256 ? 4.5 + 2.45 * chunks : 5.5 + 3.3 * many + std::max(3.4, 7.4 * many) * chunks;
-    return us * 1e-6 < (plan.splits > 1 ? 0.85 : 1.0) * plan_seconds(plan, m, n, k, batch);
+    if (us * 1e-6 >= (plan.splits > 1 ? 0.85 : 1.0) * plan_seconds(plan, m, n, k, batch))
+        return false;
+    return whose == PlanOf::kLibrary || same_plan(plan, choose_plan(m, n, k, batch, kAnyWorkspace));
 }
 
-// The product under `plan` (unless forced, skinny and small products take
-// their own kernels); a split plan keeps its partial sums in `ext`,
+// The product under `plan` (unless it is the caller's, skinny and small products
+// take their own kernels); a split plan keeps its partial sums in `ext`,
 // which must hold the plan's workspace bytes.  Allocates nothing.
 pam_status_t run_gemm(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t k, const float *A, int64_t lda,
                       int64_t sa, const float *B, int64_t ldb, int64_t sb, float *C, int64_t ldc, int64_t sc,
-                      int64_t batch, const Plan &plan, hipStream_t stream, int round_drop = 0,
-                      const Workspace *ext = nullptr, bool bf16 = false, bool forced_plan = false) {
+                      int64_t batch, const Plan &plan, PlanOf whose, hipStream_t stream, int round_drop = 0,
+                      const Workspace *ext = nullptr, bool bf16 = false) {
     if (m == 0 || n == 0 || batch == 0)
         return PAM_SUCCESS;
     Layout L{};
@@ -527,14 +533,14 @@ pam_status_t run_gemm(pam_op_t ta, pam_op_t tb, int64_t m, int64_t n, int64_t k,
     p.splits = (int32_t)L.splits;
     float *ws = L.ws_bytes > 0 ? static_cast<float *>(ext->ptr) : nullptr;
 
-    if (!forced_plan && skinny_product(ta, tb, plan, m, n, k, batch)) {
+    if (whose != PlanOf::kCaller && skinny_product(ta, tb, plan, m, n, k, batch)) {
         p.A = A;
         p.B = B;
         p.C = C;
         const hipError_t e = pamk::launch_pam_skinny(m <= n, bf16, p, batch, stream);
         return e == hipSuccess ? PAM_SUCCESS : fail_hip(e, "skinny product kernel launch");
     }
-    if (!forced_plan && small_product(plan, m, n, k, batch)) {
+    if (whose != PlanOf::kCaller && small_product(plan, whose, m, n, k, batch)) {
         p.A = A;
         p.B = B;
         p.C = C;
@@ -791,7 +797,8 @@ pam_status_t pam_gemm(pam_op_t transA, pam_op_t transB, int64_t m, int64_t n, in
         return st;
     if (m == 0 || n == 0)
         return PAM_SUCCESS;
-    return run_gemm(transA, transB, m, n, k, A, lda, 0, B, ldb, 0, C, ldc, 0, 1, choose_plan(m, n, k, 1, 0), stream);
+    return run_gemm(transA, transB, m, n, k, A, lda, 0, B, ldb, 0, C, ldc, 0, 1, choose_plan(m, n, k, 1, 0),
+                    PlanOf::kLimited, stream);
 }
 
 pam_status_t pam_gemm_batched(pam_op_t transA, pam_op_t transB, int64_t m, int64_t n, int64_t k, const float *A,
@@ -803,7 +810,7 @@ pam_status_t pam_gemm_batched(pam_op_t transA, pam_op_t transB, int64_t m, int64
     if (m == 0 || n == 0 || batch == 0)
         return PAM_SUCCESS;
     return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch,
-                    choose_plan(m, n, k, batch, 0), stream);
+                    choose_plan(m, n, k, batch, 0), PlanOf::kLimited, stream);
 }
 
 pam_status_t pam_gemm_narrow(pam_op_t transA, pam_op_t transB, int64_t m, int64_t n, int64_t k, const float *A,
@@ -818,7 +825,7 @@ pam_status_t pam_gemm_narrow(pam_op_t transA, pam_op_t transB, int64_t m, int64_
     if (m == 0 || n == 0 || batch == 0)
         return PAM_SUCCESS;
     return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch,
-                    choose_plan(m, n, k, batch, 0), stream, 23 - mantissa_bits);
+                    choose_plan(m, n, k, batch, 0), PlanOf::kLimited, stream, 23 - mantissa_bits);
 }
 
 pam_status_t pam_gemm_batched_noalloc(pam_op_t transA, pam_op_t transB, int64_t m, int64_t n, int64_t k,
@@ -855,8 +862,8 @@ pam_status_t pam_gemm_batched_noalloc(pam_op_t transA, pam_op_t transB, int64_t 
             return fail_hip(e, "hipGetSymbolAddress of the static scratch");
     }
     const Workspace ws{scratch, pamk::kScratchBytes};
-    return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, plan, stream,
-                    23 - mantissa_bits, &ws);
+    return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, plan,
+                    PlanOf::kLimited, stream, 23 - mantissa_bits, &ws);
 }
 
 pam_status_t pam_gemm_workspace_size(int64_t m, int64_t n, int64_t k, int64_t batch, size_t *bytes) {
@@ -893,7 +900,7 @@ pam_status_t pam_gemm_batched_ws(pam_op_t transA, pam_op_t transB, int64_t m, in
         return PAM_SUCCESS;
     const Workspace ws{workspace, workspace_bytes};
     return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch,
-                    choose_plan(m, n, k, batch, kAnyWorkspace), stream, 23 - mantissa_bits, &ws);
+                    choose_plan(m, n, k, batch, kAnyWorkspace), PlanOf::kLibrary, stream, 23 - mantissa_bits, &ws);
 }
 
 pam_status_t pam_gemm_batched_bf16(pam_op_t transA, pam_op_t transB, int64_t m, int64_t n, int64_t k,
@@ -909,7 +916,8 @@ pam_status_t pam_gemm_batched_bf16(pam_op_t transA, pam_op_t transB, int64_t m, 
         return PAM_SUCCESS;
     const Workspace ws{workspace, workspace_bytes};
     return run_gemm(transA, transB, m, n, k, a, lda, strideA, b, ldb, strideB, C, ldc, strideC, batch,
-                    choose_plan(m, n, k, batch, workspace != nullptr ? kAnyWorkspace : 0), stream, 0,
+                    choose_plan(m, n, k, batch, workspace != nullptr ? kAnyWorkspace : 0),
+                    workspace != nullptr ? PlanOf::kLibrary : PlanOf::kLimited, stream, 0,
                     workspace != nullptr ? &ws : nullptr, true);
 }
 
@@ -1061,18 +1069,18 @@ pam_status_t pam_gemm_batched_with_plan(pam_op_t transA, pam_op_t transB, int64_
     // K slices (a multiple of 16 steps per k-group; a plan of the caller's takes
     // multiples of 16).
     const Plan given{plan->tile_m, plan->tile_n, plan->kgroups, plan->splits, 0, plan->whole_tiles};
-    bool forced = true;
-    for (const size_t limit : {kAnyWorkspace, (size_t)0}) {
-        const Plan own = choose_plan(m, n, std::max<int64_t>(k, 1), batch, limit);
+    PlanOf whose = PlanOf::kCaller;
+    for (const PlanOf who : {PlanOf::kLibrary, PlanOf::kLimited}) {
+        const Plan own = choose_plan(m, n, std::max<int64_t>(k, 1), batch, who == PlanOf::kLibrary ? kAnyWorkspace : 0);
         if (same_plan(given, own)) {
             p = own;
-            forced = false;
+            whose = who;
             break;
         }
     }
     const Workspace ws{workspace, workspace_bytes};
-    return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, p, stream, 0,
-                    &ws, false, forced);
+    return run_gemm(transA, transB, m, n, k, A, lda, strideA, B, ldb, strideB, C, ldc, strideC, batch, p, whose,
+                    stream, 0, &ws);
 }
 
 pam_status_t pam_device_info(int device, pam_device_info_t *info) {
