@@ -29,6 +29,24 @@ def to_dev(x: np.ndarray):
     return torch.from_numpy(np.ascontiguousarray(x)).to(device())
 
 
+def tiled(plan, m: int, n: int, k: int, batch: int = 1) -> tuple:
+    """`plan` (tile_m, tile_n, splits[, kgroups[, whole_tiles]]) as one that runs
+    the tile shape it names: a plan equal to the library's own choice for these
+    sizes runs as the library does, which for small products and few rows is
+    another kernel.  A whole-tile count beside one split, or one more slice,
+    makes it the caller's."""
+    import paper_2305_17190_amd as pam
+    tm, tn, splits, kg, whole = tuple(plan) + (1, 0)[len(plan) - 3:]
+    own = {pam.plan(m, n, k, batch), pam.plan(m, n, k, batch, max_workspace_bytes=0)}
+    if (tm, tn, splits, kg, whole) in own:
+        if splits == 1:
+            whole += 1
+        else:
+            splits += 1
+    assert (tm, tn, splits, kg, whole) not in own
+    return tm, tn, splits, kg, whole
+
+
 def oracle_gemm(a_buf, b_buf, ta, tb, m, n, k, lda, ldb, stride_a=0, stride_b=0, batches=None, rows=None,
                 cols=None):
     """C and S from the C oracle over flat operand buffers (float64)."""

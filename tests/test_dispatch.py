@@ -142,9 +142,17 @@ def parameters(function, names):
             for case in mark.args[1]]
 
 
-def test_gpu_tests_reach_the_few_row_kernel():
-    """The sizes of the kernel's GPU tests do go to it."""
+def test_gpu_tests_reach_the_kernels_they_name():
+    """The sizes of the GPU tests of each kernel do go to that kernel."""
+    import test_gpu_bf16
     import test_gpu_skinny
+    import test_gpu_small
+    layouts = ((False, False), (False, True), (True, False), (True, True))
+    sizes = parameters(test_gpu_small.test_sizes_and_layouts, "m,n,k")
+    assert len(sizes) >= 9
+    for m, n, k in sizes + [(70, 66, 300), (64, 64, 128), (45, 77, 203), (33, 40, 5)]:
+        for ta, tb in layouts:
+            assert names(probe.product(m, n, k, ta=ta, tb=tb)) == ["small"], (m, n, k, ta, tb)
     fews = parameters(test_gpu_skinny.test_row_counts_widths_and_k, "few")
     wides = parameters(test_gpu_skinny.test_row_counts_widths_and_k, "wide,k")
     assert len(fews) >= 10 and len(wides) >= 6
@@ -157,12 +165,8 @@ def test_gpu_tests_reach_the_few_row_kernel():
     assert len(long_k) >= 4
     for few, wide, k in long_k:
         assert names(probe.product(few, wide, k, workspace=False)) == ["few rows"]
-
-
-def test_gpu_tests_reach_the_small_product_kernel():
-    import test_gpu_small
-    sizes = parameters(test_gpu_small.test_sizes_and_layouts, "m,n,k")
-    assert len(sizes) >= 9
-    for m, n, k in sizes + [(70, 66, 300), (64, 64, 128), (45, 77, 203), (33, 40, 5)]:
-        for ta, tb in ((False, False), (False, True), (True, False), (True, True)):
-            assert names(probe.product(m, n, k, ta=ta, tb=tb)) == ["small"], (m, n, k, ta, tb)
+    for shape, kind in test_gpu_bf16.PLAN_SHAPES:
+        for size in (shape, (*(-(-d // 8) * 8 for d in shape[:3]), shape[3])):
+            for ta, tb in layouts:
+                got = probe.product(*size, ta=ta, tb=tb, bf16=True)[0]
+                assert (got.name, got.tile_m, got.tile_n, got.kgroups) == ("tiled", *kind[:3]), (size, ta, tb)

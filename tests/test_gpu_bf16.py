@@ -60,8 +60,8 @@ def test_bf16_products(m, n, k, batch, ta, tb, kinds):
 
 
 def test_bf16_unaligned_rows_and_views():
-    # A starting 2 bytes past an 8-byte boundary and padded rows: the loader's
-    # element-by-element path
+    # A starting 2 bytes past an 8-byte boundary and padded rows: copies at any
+    # alignment
     import torch
     note("bf16 gemm on offset / padded views")
     base = bf16_bits((1, 91 * 77 + 1), 5).to(device())[0]
@@ -113,7 +113,7 @@ def test_bf16_argument_rules():
 # split (none, split K, whole-K tiles then split ones): (m, n, k, batch) ->
 # (tile_m, tile_n, kgroups, splits K, has whole-K tiles).  Each tile shape and
 # operand layout has its own map from the copies a wave makes to the segments
-# its lanes stage.
+# its lanes stage.  (Sizes that the small-product kernel leaves to their plan.)
 PLAN_SHAPES = [
     ((150, 2500, 40, 8), (128, 128, 1, False, False)),
     ((150, 70, 5000, 8), (128, 128, 1, True, False)),
@@ -121,8 +121,8 @@ PLAN_SHAPES = [
     ((1200, 300, 1000, 8), (128, 64, 1, True, True)),
     ((70, 1200, 5000, 1), (128, 64, 1, True, False)),
     ((70, 2500, 40, 8), (128, 64, 2, False, False)),
-    ((70, 70, 1000, 1), (128, 64, 2, True, False)),
-    ((70, 70, 40, 1), (64, 64, 4, False, False)),
+    ((70, 70, 2000, 1), (128, 64, 2, True, False)),
+    ((70, 1200, 40, 8), (64, 64, 4, False, False)),
     ((70, 70, 20000, 1), (64, 64, 4, True, False)),
     ((150, 1200, 5000, 2), (64, 64, 1, True, False)),
 ]
@@ -134,9 +134,9 @@ PLAN_SHAPES = [
 @pytest.mark.parametrize("shape,kind", PLAN_SHAPES, ids=lambda v: "x".join(map(str, v)) if len(v) == 4 else None)
 def test_bf16_every_tile_and_layout(shape, kind, ta, tb, aligned):
     # Bit for bit the product of the widened float32 operands under every plan
-    # kind and layout, with ragged tile edges in M and N and a K tail; rows of
-    # a multiple of 8 elements take the 16-byte copies, the others the
-    # element-by-element loads.
+    # kind and layout, with ragged tile edges in M and N and a K tail; with sizes
+    # that are no multiple of 8 elements the last 16-byte copies of a row start
+    # earlier, so as to end with it.
     import torch
     m, n, k, batch = shape
     if aligned:

@@ -22,7 +22,7 @@ import pytest
 
 import pam_workloads as wl
 import paper_2305_17190_amd as pam
-from gpu_util import device, note, oracle_gemm, to_dev
+from gpu_util import device, note, oracle_gemm, tiled, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -154,9 +154,10 @@ def test_underflow_tie_is_zero(tile, order):
     a[:, 17] = sa * lo
     b[17, :] = sb * hi
     tm, tn, splits, kg = tile
-    c = pam.bmm(to_dev(a[None]), to_dev(b[None]), plan=(tm, tn, splits, kg, 0)).cpu().numpy()[0]
+    c = pam.bmm(to_dev(a[None]), to_dev(b[None]), plan=tiled((tm, tn, splits, kg, 0), m, n, k)).cpu().numpy()[0]
     c_ref, _ = pam_ref.pam_gemm_ref(a, b)
     assert np.array_equal(c.astype(np.float64), c_ref)
     # K = 1: the tie pair alone gives zeros
-    c1 = pam.bmm(to_dev(a[None, :, 17:18]), to_dev(b[None, 17:18, :]), plan=(tm, tn, 1, kg, 0)).cpu().numpy()[0]
+    c1 = pam.bmm(to_dev(a[None, :, 17:18]), to_dev(b[None, 17:18, :]),
+                 plan=tiled((tm, tn, 1, kg, 0), m, n, 1)).cpu().numpy()[0]
     assert np.all(c1 == 0.0), f"{int((c1 != 0).sum())} outputs nonzero, e.g. {c1[c1 != 0][:3]}"

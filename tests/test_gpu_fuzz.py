@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 import paper_2305_17190_amd as pam
-from gpu_util import check_gemm, device, note, oracle_gemm, to_dev
+from gpu_util import check_gemm, device, note, oracle_gemm, tiled, to_dev
 from oracle import pam_ref
 
 pytestmark = pytest.mark.gpu
@@ -61,6 +61,7 @@ def test_random_products(case):
             buf[idx[0::3]] = 0.0
             buf[idx[1::3]] = np.float32(3e-41)
             buf[idx[2::3]] = np.float32(1.5e-38)
+    plan = plan and tiled(plan, m, n, k, batch)
     note(f"fuzz {case}: m={m} n={n} k={k} batch={batch} ta={ta} tb={tb} pad={pad} plan={plan}")
     da = torch.as_strided(to_dev(a_buf), (batch, a_rows, a_cols), (sa, lda, 1))
     db = torch.as_strided(to_dev(b_buf), (batch, b_rows, b_cols), (sb, ldb, 1))
@@ -108,6 +109,7 @@ def test_random_large_products(case):
             buf[idx[0::3]] = 0.0
             buf[idx[1::3]] = np.float32(3e-41)
             buf[idx[2::3]] = np.float32(1.5e-38)
+    plan = tiled(plan, m, n, k)
     note(f"fuzz large {case}: m={m} n={n} k={k} ta={ta} tb={tb} plan={plan} tiles={tiles}")
     da = to_dev(a_buf).view(1, a_rows, a_cols)
     db = to_dev(b_buf).view(1, b_rows, b_cols)

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import paper_2305_17190_amd as pam
-from gpu_util import check_gemm, device, note, oracle_gemm, to_dev
+from gpu_util import check_gemm, device, note, oracle_gemm, tiled, to_dev
 from oracle import pam_ref
 
 pytestmark = pytest.mark.gpu
@@ -59,6 +59,8 @@ def run_case(m, n, k, ta, tb, kind_a, kind_b, plan=None, pad=(0, 0, 0), seed=0, 
     b_buf = make(kind_b, (batch, b_rows, b_cols + pad[1]), seed + 1)
     lda, ldb = a_cols + pad[0], b_cols + pad[1]
     ldc = n + pad[2]
+    if plan is not None:
+        plan = tiled(plan, m, n, k, batch)
     note(f"gemm m={m} n={n} k={k} ta={ta} tb={tb} A={kind_a} B={kind_b} plan={plan} pad={pad} batch={batch}")
     da = to_dev(a_buf)[:, :, :a_cols]
     db = to_dev(b_buf)[:, :, :b_cols]
@@ -138,7 +140,7 @@ def test_identity_is_exact():
     a = g.standard_normal((150, 140)).astype(np.float32)
     eye = np.eye(140, dtype=np.float32)
     for plan in PLANS:
-        c = pam.bmm(to_dev(a[None]), to_dev(eye[None]), plan=plan).cpu().numpy()[0]
+        c = pam.bmm(to_dev(a[None]), to_dev(eye[None]), plan=tiled(plan, 150, 140, 140)).cpu().numpy()[0]
         assert np.array_equal(c.view(np.uint32), a.view(np.uint32)), f"identity not exact with plan {plan}"
 
 
@@ -173,6 +175,7 @@ def test_leading_dimensions_near_the_limit(ta, plan):
     if plan is None:
         c = pam.gemm(da, db, trans_a=ta).cpu().numpy()
     else:
+        plan = tiled(plan, m, n, k)
         c = pam.bmm(da.unsqueeze(0), db.unsqueeze(0), trans_a=ta, plan=plan).cpu().numpy()[0]
     del da, db
     c_ref, s_ref = oracle_gemm(a_buf, b_buf, ta, False, m, n, k, ld, ld)
@@ -222,9 +225,10 @@ def test_whole_and_split_tiles_match_their_plans(tile, kg, batch):
     tiles_m, tiles_n = -(-m // bm), -(-n // bn)
     total = batch * tiles_m * tiles_n
     whole = total // 2 + 1
-    unsplit = pam.bmm(a, b, plan=(bm, bn, 1, kg))
-    split = pam.bmm(a, b, plan=(bm, bn, 4, kg))
-    mixed = pam.bmm(a, b, plan=(bm, bn, 4, kg, whole))
+    unsplit = pam.bmm(a, b, plan=tiled((bm, bn, 1, kg), m, n, k, batch))
+    plans = (bm, bn, 4, kg), (bm, bn, 4, kg, whole)
+    assert all(tiled(p, m, n, k, batch)[2] == 4 for p in plans)   # neither is the library's own
+    split, mixed = (pam.bmm(a, b, plan=p) for p in plans)
     assert not torch.equal(unsplit.view(torch.int32), split.view(torch.int32))
     for t in range(total):
         z, r = divmod(t, tiles_m * tiles_n)
@@ -253,8 +257,8 @@ def test_small_and_large_launches_agree(ta, tb):
     b = make("normal", b_shape, 92)
     a[7] = make("specials", a_shape[1:], 93)
     da, db = to_dev(a), to_dev(b)
-    small = pam.bmm(da[:80], db[:80], trans_a=ta, trans_b=tb, plan=plan)
-    large = pam.bmm(da, db, trans_a=ta, trans_b=tb, plan=plan)
+    small = pam.bmm(da[:80], db[:80], trans_a=ta, trans_b=tb, plan=tiled(plan, m, n, k, 80))
+    large = pam.bmm(da, db, trans_a=ta, trans_b=tb, plan=tiled(plan, m, n, k, 120))
     same_nan = torch.isnan(small) == torch.isnan(large[:80])
     assert bool(same_nan.all())
     fin = ~torch.isnan(small)
@@ -338,6 +342,7 @@ def test_exact_sums_underflowing_products_add_nothing(decoys, plan, ta, tb):
     result must equal the oracle bit for bit.  A product that underflows
     (below 2^-126) is zero by definition; adding anything for it would show."""
     m, n, k = 150, 140, 300
+    plan = tiled(plan, m, n, k)
     note(f"exact pow2 sums decoys={decoys} plan={plan} ta={ta} tb={tb}")
     a_op = pow2_operands((m, k), 81, decoys[0])
     b_op = pow2_operands((k, n), 82, decoys[1])
@@ -377,6 +382,7 @@ def test_special_beside_low_in_one_segment(operand, ta, tb, plan):
     # special value must not hide behind the low one, nor the low one behind
     # the special) and the other chunks and tiles their own paths.
     m, n, k = 150, 140, 96
+    plan = tiled(plan, m, n, k)
     for case, (low, special) in enumerate(SEGMENT_MIXES):
         a_shape = (k, m) if ta else (m, k)
         b_shape = (n, k) if tb else (k, n)
@@ -406,6 +412,7 @@ def test_low_values_in_one_half_of_the_tile_rows(where, plan, ta, tb):
     # sums are exact in any order: equal to the oracle bit for bit.
     import pam_workloads as wl
     m, n, k = 150, 140, 200
+    plan = tiled(plan, m, n, k)
     tm = plan[0]
     note(f"low values in {where} rows plan={plan} ta={ta} tb={tb}")
     a_op = wl.exact_sum_values((m, k), 901, 0.0, 0.0)

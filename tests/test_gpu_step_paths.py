@@ -15,7 +15,7 @@ import numpy as np
 import pytest
 
 import paper_2305_17190_amd as pam
-from gpu_util import check_gemm, note, oracle_gemm, to_dev
+from gpu_util import check_gemm, note, oracle_gemm, tiled, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -47,6 +47,7 @@ def planted_operands(seed):
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)])
 def test_every_two_op_step_count(ta, tb, plan):
     a, b = planted_operands(31)
+    plan = tiled(plan, M, N, K)
     note(f"step paths ta={ta} tb={tb} plan={plan} m={M} n={N} k={K}")
     a_buf = np.ascontiguousarray(a.T if ta else a)
     b_buf = np.ascontiguousarray(b.T if tb else b)
@@ -67,6 +68,7 @@ def test_dense_zeros_with_tiny_values(ta, tb, plan, share):
     denormals among them, and in A's first 40 rows and B's first 40 columns
     tiny normals, whose steps round each product on its own."""
     g = np.random.default_rng(int(share * 100))
+    plan = tiled(plan, M, N, K)
     a, b = g.standard_normal((M, K)).astype(np.float32), g.standard_normal((K, N)).astype(np.float32)
     for x in (a, b):
         u = g.random(x.shape)
