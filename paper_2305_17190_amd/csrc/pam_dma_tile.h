@@ -128,11 +128,16 @@ struct DmaTile {
     }
     // What a tile's copies have to heed, the same for the whole workgroup:
     // kEdge when a piece of it straddles the last column of an operand that is
-    // not K-contiguous, kShort when a row of the operand (up to k = ke, or its
-    // o_lim columns) is shorter than a piece.
-    static constexpr uint32_t kEdge = 1u, kShort = 2u;
-    static __device__ __forceinline__ uint32_t kind(int ke, int o0, int o_lim) {
-        return (KCONTIG || o0 + D <= o_lim || o_lim % EPC == 0 ? 0u : kEdge) | ((KCONTIG ? ke : o_lim) >= EPC ? 0u : kShort);
+    // not K-contiguous; kThin when such an operand has fewer columns than a
+    // piece; kShort when a K-contiguous row (up to k = ke) is shorter than a
+    // piece, or the whole thin operand.
+    static constexpr uint32_t kEdge = 1u, kShort = 2u, kThin = 3u;
+    static __device__ __forceinline__ uint32_t kind(int ke, int o0, int o_lim, int64_t ld) {
+        if (KCONTIG)
+            return ke >= EPC ? 0u : kShort;
+        if (o_lim < EPC)
+            return (int64_t)(ke - 1) * ld + o_lim >= EPC ? kThin : kShort;
+        return o0 + D <= o_lim || o_lim % EPC == 0 ? 0u : kEdge;
     }
 
     // At the last k steps of a row, or at the last columns, a piece that
@@ -143,12 +148,24 @@ struct DmaTile {
     // piece that would start at x; below zero by at most EPC - 1.
     static __device__ __forceinline__ int piece_k(int kk, int k_rem) { return min(kk, k_rem - EPC); }
     static __device__ __forceinline__ int piece_o(int o, int o0, int o_lim) { return min(o, o_lim - EPC - o0); }
+    // kThin: first element, from the chunk's base, of the piece of row kk <
+    // k_rem.  It runs on over the gap and the rows after it; at the operand's
+    // last element (BK rows on suffices) it starts earlier instead.
+    // (Copied element by element such an operand held up every chunk: 4096 x 3 x
+    // 4096 74.8 us, now 57.9 us; x 4, whole pieces, 50.6 us.)
+    static __device__ __forceinline__ int piece_thin(int kk, int64_t ld, int o_lim, int k_rem) {
+        const uint32_t row = __umul24((uint32_t)kk, (uint32_t)ld);
+        return min((int)row, (int)__umul24((uint32_t)min(k_rem - 1, BK), (uint32_t)ld) + o_lim - EPC);
+    }
     // As boff, from EPC elements before the chunk's base.
-    static __device__ __forceinline__ uint32_t boff_edge(int tid, int r, int64_t ld, int o0, int o_lim, int k_rem) {
+    static __device__ __forceinline__ uint32_t boff_edge(int tid, int r, int64_t ld, int o0, int o_lim, int k_rem,
+                                                         uint32_t kind) {
         const int o = copy_o(tid, r);
         const int kk = copy_k(tid, r);
         const uint32_t es = (uint32_t)sizeof(T);
         const uint32_t ldb = (uint32_t)ld * es;
+        if (!KCONTIG && kind == kThin)
+            return (uint32_t)(piece_thin(min(kk, k_rem - 1), ld, o_lim, k_rem) + EPC) * es;
         if (KCONTIG)
             return __umul24((uint32_t)min(o, o_lim - 1 - o0), ldb) + (uint32_t)(piece_k(kk, k_rem) + EPC) * es;
         return __umul24((uint32_t)min(kk, k_rem - 1), ldb) + (uint32_t)(piece_o(o, o0, o_lim) + EPC) * es;
@@ -182,13 +199,12 @@ struct DmaTile {
         // Edges are rare: their addresses are worked out here, never kept.
         asm volatile("" : "+v"(tid), "+s"(o0), "+s"(o_lim), "+s"(ld));
         cb -= 16;
-        if (kind & kShort) {
-            // Rows shorter than a piece: its elements one by one, those
-            // before the row's first as zeros.
+        if (kind == kShort) {
+            // Its elements one by one, those before the row's first as zeros.
             const int before = KCONTIG ? EPC - k_rem : EPC - (o_lim - o0);
 #pragma unroll 1
             for (int r = 0; r < CL; ++r) {
-                const char *src = cb + boff_edge(tid, r, ld, o0, o_lim, k_rem);
+                const char *src = cb + boff_edge(tid, r, ld, o0, o_lim, k_rem, kind);
                 const uint32_t dst = lds_w + RAW_OFF + (uint32_t)(r * NW) * 1024u + (uint32_t)(tid & 63) * 16u;
 #pragma unroll 1
                 for (int x = 0; x < EPC; ++x)
@@ -197,12 +213,12 @@ struct DmaTile {
             }
             return;
         }
-        dma_copy16<RAW_OFF>(cb, boff_edge(tid, 0, ld, o0, o_lim, k_rem), lds_w);
+        dma_copy16<RAW_OFF>(cb, boff_edge(tid, 0, ld, o0, o_lim, k_rem, kind), lds_w);
         if constexpr (CL >= 2)
-            dma_copy16<RAW_OFF + NW * 1024>(cb, boff_edge(tid, 1, ld, o0, o_lim, k_rem), lds_w);
+            dma_copy16<RAW_OFF + NW * 1024>(cb, boff_edge(tid, 1, ld, o0, o_lim, k_rem, kind), lds_w);
         if constexpr (CL == 4) {
-            dma_copy16<RAW_OFF + 2 * NW * 1024>(cb, boff_edge(tid, 2, ld, o0, o_lim, k_rem), lds_w);
-            dma_copy16<RAW_OFF + 3 * NW * 1024>(cb, boff_edge(tid, 3, ld, o0, o_lim, k_rem), lds_w);
+            dma_copy16<RAW_OFF + 2 * NW * 1024>(cb, boff_edge(tid, 2, ld, o0, o_lim, k_rem, kind), lds_w);
+            dma_copy16<RAW_OFF + 3 * NW * 1024>(cb, boff_edge(tid, 3, ld, o0, o_lim, k_rem, kind), lds_w);
         }
     }
 
@@ -218,9 +234,7 @@ struct DmaTile {
         const int half = KCONTIG ? (lane >> 4) & 1 : lane & 1;
         return (uint32_t)(((q / 64) * NW + w) * 256 + (q % 64) * 4 + half * 2);
     }
-    // Reads through an LDS-space pointer: the compiler then cannot merge a
-    // landing-buffer read with the element-by-element global loads of the
-    // other branch into one generic (flat) load.
+    // Reads through an LDS-space pointer: never a generic (flat) load.
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
@@ -237,20 +251,41 @@ struct DmaTile {
         return make_uint4(d.x << 16, d.x & 0xFFFF0000u, d.y << 16, d.y & 0xFFFF0000u);
     }
 
-    // Element x of the piece that holds segment r.
-    static __device__ __forceinline__ uint32_t piece_element(const uint32_t *raw, int w, int lane, int r, int x) {
-        uint32_t slot = slot_of(w, lane, r);
-        if constexpr (!kWide)
-            slot = 2u * (slot & ~3u);   // the piece's first element
-        return widen(((const lds_t *)raw)[slot + (uint32_t)x]);
+    // Segment r's elements from element x of the piece that holds it (0 <= x <
+    // EPC; elements past the piece's end are of no meaning).
+    static __device__ __forceinline__ uint4 piece_elements(const uint32_t *raw, int w, int lane, int r, uint32_t x) {
+        const u32x4 q = *(lds_u32x4 *)(raw + (slot_of(w, lane, r) & ~3u));
+        uint32_t q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+        if constexpr (kWide) {
+            if (x & 1u) {
+                q0 = q1;
+                q1 = q2;
+                q2 = q3;
+            }
+            return (x & 2u) ? make_uint4(q2, q3, q3, q3) : make_uint4(q0, q1, q2, q3);
+        }
+        if (x & 4u) {
+            q0 = q2;
+            q1 = q3;
+        }
+        if (x & 2u) {
+            q0 = q1;
+            q1 = q2;
+            q2 = q3;
+        }
+        if (x & 1u) {
+            q0 = __builtin_amdgcn_alignbit(q1, q0, 16);
+            q1 = __builtin_amdgcn_alignbit(q2, q1, 16);
+        }
+        return make_uint4(q0 << 16, q0 & 0xFFFF0000u, q1 << 16, q1 & 0xFFFF0000u);
     }
 
     // The thread's segments of a chunk with k_rem valid k steps (the elements
     // past them are zero; columns past o_lim repeat the last one, their
     // outputs are discarded) from the landing buffer.
     template <int EDGE>
-    __device__ __forceinline__ void fetch(const uint32_t *raw, int w, int o0, int o_lim, int k_rem, uint32_t kind,
-                                          int tid) {
+    __device__ __forceinline__ void fetch(const uint32_t *raw, int w, int64_t ld, int o0, int o_lim, int k_rem,
+                                          uint32_t kind, int tid) {
         if (EDGE < 2 || (k_rem >= BK && kind == 0u)) {
             // The common case, one branch for all segments: the reads issue
             // back to back and are waited for once.
@@ -261,27 +296,32 @@ struct DmaTile {
                 blank(o_lim - o0, tid);
             return;
         }
-        asm volatile("" : "+v"(tid), "+s"(o0), "+s"(o_lim), "+s"(w));   // as in copy()
+        asm volatile("" : "+v"(tid), "+s"(o0), "+s"(o_lim), "+s"(ld), "+s"(w));   // as in copy()
+        // One read per piece and selects for all lanes, moved or not.  (Element by
+        // element, behind a branch each, a bfloat16 4096 x 9 x 4096 product took
+        // 59.5 us, now 56.7 us.)
 #pragma unroll
         for (int r = 0; r < L; ++r) {
             const int o = seg_o(tid, r);
             const int kk = seg_k(tid, r);
-            const bool unmoved = KCONTIG ? (kk & -EPC) + EPC <= k_rem
-                                         : kk < k_rem && (o & -EPC) + EPC <= o_lim - o0;
-            if (unmoved) {   // its piece lies where it does inside the operand
-                v[r] = read_slot(raw, slot_of(w, tid & 63, r));
-                continue;
-            }
-            uint32_t e[4];
+            int x;   // the segment's first element in its piece
+            if (KCONTIG)
+                x = kk - piece_k(kk & -EPC, k_rem);
+            else if (kind == kThin)
+                x = o + (int)__umul24((uint32_t)min(kk, k_rem - 1), (uint32_t)ld) -
+                    piece_thin(min(kk, k_rem - 1), ld, o_lim, k_rem);
+            else
+                x = o - piece_o(o & -EPC, o0, o_lim);
+            const uint4 q = piece_elements(raw, w, tid & 63, r, (uint32_t)x);
+            uint32_t e[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const int k = KCONTIG ? kk + c : kk;
-                const int x = KCONTIG ? k - piece_k(kk & -EPC, k_rem)
-                                      : min(o + c, o_lim - 1 - o0) - piece_o(o & -EPC, o0, o_lim);
-                e[c] = 0u;
-                if (k < k_rem)
-                    e[c] = piece_element(raw, w, tid & 63, r, x);
+                if (!KCONTIG && c > 0)
+                    e[c] = o + c < o_lim - o0 ? e[c] : e[c > 0 ? c - 1 : 0];
             }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                e[c] = (KCONTIG ? kk + c : kk) < k_rem ? e[c] : 0u;
             v[r] = make_uint4(e[0], e[1], e[2], e[3]);
         }
         blank(o_lim - o0, tid);
@@ -301,9 +341,6 @@ struct DmaTile {
             }
         }
     }
-
-    static __device__ __forceinline__ uint32_t widen(float x) { return __float_as_uint(x); }
-    static __device__ __forceinline__ uint32_t widen(uint16_t h) { return (uint32_t)h << 16; }
 
     // Round every held element to 23 - drop mantissa bits, nearest even (inf
     // and NaN unchanged).

@@ -187,7 +187,7 @@ pam_exact_grad_kernel(GemmParams p) {
 
     // The copies' kinds (A's, then B's) as one scalar word, tested afresh in
     // each chunk (conditions kept across the loop took lane masks, spilled).
-    const uint32_t kinds = TileA::kind(ke, m0, p.m) | TileB::kind(ke, n0, p.n) << 2;
+    const uint32_t kinds = TileA::kind(ke, m0, p.m, p.lda) | TileB::kind(ke, n0, p.n, p.ldb) << 2;
     if (nchunks > 0) {
         TileA::template copy<0, 2>(a_base, lds_w, tid, p.lda, m0, p.m, ke - kb, kinds & 3u);
         TileB::template copy<kRawA * 4, 2>(b_base, lds_w, tid, p.ldb, n0, p.n, ke - kb, kinds >> 2);
@@ -278,8 +278,8 @@ pam_exact_grad_kernel(GemmParams p) {
         asm volatile("" : "+v"(tid_c));
         __builtin_amdgcn_s_setprio(1);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's copies of chunk c have landed
-        la.template fetch<2>(rawA, wave, m0, p.m, k_rem, kd & 3u, tid_c);
-        lb.template fetch<2>(rawB, wave, n0, p.n, k_rem, kd >> 2, tid_c);
+        la.template fetch<2>(rawA, wave, p.lda, m0, p.m, k_rem, kd & 3u, tid_c);
+        lb.template fetch<2>(rawB, wave, p.ldb, n0, p.n, k_rem, kd >> 2, tid_c);
         uint32_t smin[TileB::L];
         const uint32_t mx = lb.scan(smin);
         static_assert(TileB::L == 1, "one B segment per thread");

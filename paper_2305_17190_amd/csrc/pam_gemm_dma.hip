@@ -319,7 +319,7 @@ pam_gemm_dma_kernel(GemmParams p) {
 
     // The copies' kinds (A's, then B's) as one scalar word, tested afresh in
     // each chunk (conditions kept across the loop took lane masks, spilled).
-    const uint32_t kinds = EDGE < 2 ? 0u : TileA::kind(ke, m0, p.m) | TileB::kind(ke, n0, p.n) << 2;
+    const uint32_t kinds = EDGE < 2 ? 0u : TileA::kind(ke, m0, p.m, p.lda) | TileB::kind(ke, n0, p.n, p.ldb) << 2;
     if (nchunks > 0) {
         TileA::template copy<0, EDGE>(a_base, lds_w, tid, p.lda, m0, p.m, ke - kb, kinds & 3u);
         TileB::template copy<kRawA * 4, EDGE>(b_base, lds_w, tid, p.ldb, n0, p.n, ke - kb, kinds >> 2);
@@ -344,8 +344,8 @@ pam_gemm_dma_kernel(GemmParams p) {
         // This thread's copies of chunk c have landed (the only vector-memory
         // operations outstanding).
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        la.template fetch<E>(rawA, wave, m0, p.m, k_rem, kd & 3u, tid_c);
-        lb.template fetch<E>(rawB, wave, n0, p.n, k_rem, kd >> 2, tid_c);
+        la.template fetch<E>(rawA, wave, p.lda, m0, p.m, k_rem, kd & 3u, tid_c);
+        lb.template fetch<E>(rawB, wave, p.ldb, n0, p.n, k_rem, kd >> 2, tid_c);
 
         if (p.round_drop != 0) {
             la.round_mantissa(p.round_drop);

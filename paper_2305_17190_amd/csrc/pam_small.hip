@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(4)
     const T *b_base = reinterpret_cast<const T *>(p.B) + bz * p.strideB + (TB ? (int64_t)n0 * p.ldb : (int64_t)n0);
     const int64_t a_step = TA ? (int64_t)BK * p.lda : BK;
     const int64_t b_step = TB ? BK : (int64_t)BK * p.ldb;
-    const uint32_t kind_a = TileA::kind(p.k, m0, p.m), kind_b = TileB::kind(p.k, n0, p.n);
+    const uint32_t kind_a = TileA::kind(p.k, m0, p.m, p.lda), kind_b = TileB::kind(p.k, n0, p.n, p.ldb);
     const int nchunks = (p.k + BK - 1) / BK;
 
     TileA::template copy<0, 2>(a_base, lds_w, tid, p.lda, m0, p.m, p.k, kind_a);
@@ -95,8 +95,8 @@ __global__ void __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(4)
     for (int c = 0; c < nchunks; ++c) {
         const int k_rem = p.k - c * BK;   // k steps left, this chunk's included
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's copies have landed
-        la.template fetch<2>(rawA, wave, m0, p.m, k_rem, kind_a, tid);
-        lb.template fetch<2>(rawB, wave, n0, p.n, k_rem, kind_b, tid);
+        la.template fetch<2>(rawA, wave, p.lda, m0, p.m, k_rem, kind_a, tid);
+        lb.template fetch<2>(rawB, wave, p.ldb, n0, p.n, k_rem, kind_b, tid);
         if (p.round_drop != 0) {
             la.round_mantissa(p.round_drop);
             lb.round_mantissa(p.round_drop);
