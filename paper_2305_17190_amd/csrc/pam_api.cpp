@@ -101,6 +101,9 @@ constexpr int64_t kMaxHybridTiles = 1 << 20;
 constexpr int64_t kOneRoundHybridMinK = 512;
 // Most 32 x 32 tiles of a small product (small_product).
 constexpr int64_t kMaxSmallTiles = 2048;
+// Its chunk's least cost, in chunks, up to this K (small_product).
+constexpr int64_t kShortestChunkK = 32;
+constexpr double kShortestChunk = 0.7;
 // Shortest K for which a hybrid launch is taken to last at least one whole-K
 // tile (choose_plan).
 constexpr int64_t kWholeTileBoundMinK = 2048;
@@ -476,13 +479,19 @@ enum class PlanOf { kLibrary, kLimited, kCaller };
 // products: up to 256 tiles of 32 x 32 (one workgroup a compute unit) 4.5 us and
 // 2.45 us per 128 k steps; beyond, 5.5 us and 3.3 us per 1024 tiles, and per 128 k
 // steps 7.4 us per 1024 tiles, at least 3.4 us.
+// Beyond 256 tiles the copies of a chunk of up to 32 k steps (a quarter of one)
+// cost 0.7 of a whole chunk, which the plan's shorter chunks need not: 2048 of 32 x
+// 32 x 32 21.9 us, their plan 16.8 us; 640 of 19 x 96 x 21 22.7 and 15.5 us; from 33
+// k steps the kernel is the faster (794 of 10 x 50 x 55 20.3 and 25.4 us).
 // Only in place of pam_gemm_plan's plan: a product whose plan its workspace
 // limits keeps that plan.
 bool small_product(const Plan &plan, PlanOf whose, int64_t m, int64_t n, int64_t k, int64_t batch) {
     const int64_t tiles = ceil_div(m, 32) * ceil_div(n, 32) * batch;
     if (tiles > kMaxSmallTiles)
         return false;
-    const double chunks = double(k) / (pamk::kChunkK * pamk::kSmallWaves);
+    double chunks = double(k) / (pamk::kChunkK * pamk::kSmallWaves);
+    if (tiles > 256 && k <= kShortestChunkK)
+        chunks = std::max(chunks, kShortestChunk);
     const double many = double(tiles) / 1024.0;
     const double us = tiles <= 256 ? 4.5 + 2.45 * chunks : 5.5 + 3.3 * many + std::max(3.4, 7.4 * many) * chunks;
     if (us * 1e-6 >= (plan.splits > 1 ? 0.85 : 1.0) * plan_seconds(plan, m, n, k, batch))
