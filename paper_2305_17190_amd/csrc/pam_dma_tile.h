@@ -297,32 +297,42 @@ struct DmaTile {
             return;
         }
         asm volatile("" : "+v"(tid), "+s"(o0), "+s"(o_lim), "+s"(ld), "+s"(w));   // as in copy()
-        // One read per piece and selects for all lanes, moved or not.  (Element by
-        // element, behind a branch each, a bfloat16 4096 x 9 x 4096 product took
-        // 59.5 us, now 56.7 us.)
-#pragma unroll
-        for (int r = 0; r < L; ++r) {
+        // A segment out of its piece, moved or not: one read, a shift and selects
+        // for all lanes.  (Element by element, behind a branch each, a bfloat16
+        // 4096 x 9 x 4096 product took 59.5 us, now 56.7 us.)
+        auto take = [&](int r) {
             const int o = seg_o(tid, r);
             const int kk = seg_k(tid, r);
             int x;   // the segment's first element in its piece
             if (KCONTIG)
                 x = kk - piece_k(kk & -EPC, k_rem);
             else if (kind == kThin)
-                x = o + (int)__umul24((uint32_t)min(kk, k_rem - 1), (uint32_t)ld) -
-                    piece_thin(min(kk, k_rem - 1), ld, o_lim, k_rem);
+                x = o + (int)__umul24((uint32_t)kk, (uint32_t)ld) - piece_thin(kk, ld, o_lim, k_rem);
             else
                 x = o - piece_o(o & -EPC, o0, o_lim);
             const uint4 q = piece_elements(raw, w, tid & 63, r, (uint32_t)x);
             uint32_t e[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (!KCONTIG && c > 0)
+                if (KCONTIG)
+                    e[c] = kk + c < k_rem ? e[c] : 0u;
+                else if (c > 0)
                     e[c] = o + c < o_lim - o0 ? e[c] : e[c > 0 ? c - 1 : 0];
             }
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                e[c] = (KCONTIG ? kk + c : kk) < k_rem ? e[c] : 0u;
             v[r] = make_uint4(e[0], e[1], e[2], e[3]);
+        };
+        if (!KCONTIG && k_rem >= BK) {
+#pragma unroll
+            for (int r = 0; r < L; ++r)
+                take(r);
+        } else {
+            // Whole waves lie past a short K and skip their segments.
+#pragma unroll
+            for (int r = 0; r < L; ++r) {
+                v[r] = make_uint4(0u, 0u, 0u, 0u);
+                if (seg_k(tid, r) < k_rem)
+                    take(r);
+            }
         }
         blank(o_lim - o0, tid);
     }
