@@ -479,10 +479,11 @@ enum class PlanOf { kLibrary, kLimited, kCaller };
 // products: up to 256 tiles of 32 x 32 (one workgroup a compute unit) 4.5 us and
 // 2.45 us per 128 k steps; beyond, 5.5 us and 3.3 us per 1024 tiles, and per 128 k
 // steps 7.4 us per 1024 tiles, at least 3.4 us.
-// Beyond 256 tiles the copies of a chunk of up to 32 k steps (a quarter of one)
-// cost 0.7 of a whole chunk, which the plan's shorter chunks need not: 2048 of 32 x
-// 32 x 32 21.9 us, their plan 16.8 us; 640 of 19 x 96 x 21 22.7 and 15.5 us; from 33
-// k steps the kernel is the faster (794 of 10 x 50 x 55 20.3 and 25.4 us).
+// Beyond 512 tiles (two workgroups a compute unit) a chunk of up to 32 k steps
+// costs 0.7 of a whole one, mostly for copies that the plan's shorter chunks do
+// not make: 2048 of 32 x 32 x 32 21.9 us, their plan 16.8 us; 640 of 19 x 96 x 21
+// 22.7 and 15.5 us; from 33 k steps the kernel is the faster (794 of 10 x 50 x 55 20.3
+// and 25.4 us), and up to 512 tiles (4928 x 64 x 8 6.8 and 8.3 us).
 // Only in place of pam_gemm_plan's plan: a product whose plan its workspace
 // limits keeps that plan.
 bool small_product(const Plan &plan, PlanOf whose, int64_t m, int64_t n, int64_t k, int64_t batch) {
@@ -490,7 +491,7 @@ bool small_product(const Plan &plan, PlanOf whose, int64_t m, int64_t n, int64_t
     if (tiles > kMaxSmallTiles)
         return false;
     double chunks = double(k) / (pamk::kChunkK * pamk::kSmallWaves);
-    if (tiles > 256 && k <= kShortestChunkK)
+    if (tiles > 512 && k <= kShortestChunkK)
         chunks = std::max(chunks, kShortestChunk);
     const double many = double(tiles) / 1024.0;
     const double us = tiles <= 256 ? 4.5 + 2.45 * chunks : 5.5 + 3.3 * many + std::max(3.4, 7.4 * many) * chunks;

@@ -66,7 +66,8 @@ def test_long_k_small_outputs_keep_their_plan(m, n, k, batch):
 
 @pytest.mark.parametrize("m,n,k,batch,kernel", [
     (32, 32, 32, 2048, "tiled"), (19, 96, 21, 640, "tiled"), (62, 17, 27, 925, "tiled"), (6, 5, 27, 1993, "tiled"),
-    (30, 24, 24, 1004, "small"), (7, 22, 24, 1016, "small"), (10, 50, 55, 794, "small"), (8, 5, 48, 1393, "small")])
+    (30, 24, 24, 1004, "small"), (7, 22, 24, 1016, "small"), (10, 50, 55, 794, "small"), (8, 5, 48, 1393, "small"),
+    (4928, 64, 8, 1, "small"), (29, 24, 4, 300, "small"), (687, 367, 2, 1, "small")])
 def test_many_small_matrices_of_short_k(m, n, k, batch, kernel):
     """Up to 32 k steps the small-product kernel's chunk is mostly padding: many
     such matrices keep their plan."""
