@@ -164,9 +164,9 @@ typedef struct {
 /* The plan pam_gemm_batched_ws (and pam_gemm_workspace_size) uses for these
  * sizes, split K allowed.  m, n, batch > 0; k >= 0.  Two kinds of product run
  * a kernel without a plan instead (the same product, up to float32 summation
- * order): those whose operands are both K-contiguous (op N, op T) with at
- * most 32 rows of op(A) or columns of op(B), and small ones whose plan would
- * leave most of the GPU idle. */
+ * order) where the library estimates it to be the faster: those whose operands
+ * are both K-contiguous (op N, op T) with at most 32 rows of op(A) or columns of
+ * op(B), and small ones whose plan would leave most of the GPU idle. */
 pam_status_t pam_gemm_plan(int64_t m, int64_t n, int64_t k, int64_t batch, pam_plan_t *plan);
 
 /* The fastest plan (by the library's cost model) whose split-K partial sums

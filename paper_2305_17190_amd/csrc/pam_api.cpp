@@ -1,6 +1,7 @@
 // C ABI of the PAM library: argument validation, plan selection, workspace
 // handling and launches.  The arithmetic lives in the HIP sources
-// (pam_gemm_dma.hip, pam_kernels.hip, pa_ops.hip, pam_exact_grad.hip).
+// (pam_gemm_dma.hip, pam_skinny.hip, pam_small.hip, pam_exact_grad.hip,
+// pam_kernels.hip, pa_ops.hip).
 
 #include <hip/hip_runtime.h>
 #include <hsa/hsa.h>

@@ -65,7 +65,7 @@
 //   earlier, so that each lies whole inside the operand (pam_dma_tile.h), and
 //   steps past K are not run.  Before, unaligned operands and such ends were
 //   loaded element by element at the chunk boundary: the two products of a
-//   197-token attention (192 matrices, head 64) took 99.8 us, now 86.3 us.
+//   197-token attention (192 matrices, head 64) took 99 us, now 78 us.
 //
 // With k-groups (KW > 1) the groups other than the first write their
 // partial tiles to LDS, and the first group adds them in group order and
@@ -193,10 +193,6 @@ constexpr int dma_waves_per_simd(int bm, int bn, int kw) {
     return (bm == 128 && bn == 128 && kw == 1) ? 4 : (bm == 128 && bn == 64 && kw == 2) ? 3 : 2;
 }
 
-// k steps per k-group per LDS chunk: the same for every tile shape (the
-// step masks hold one bit per step of a chunk in each half of a 32-bit word).
-constexpr int dma_kpg(int, int, int) { return kChunkK; }
-
 // A chunk with more S2 steps than this (zeros in most of its k steps: ReLU
 // activations, masked probabilities, dropout) takes its S1 and S2 steps in
 // one unrolled pass of S2 steps, operands read one step ahead; with fewer,
@@ -233,7 +229,9 @@ template <int BM, int BN, int KW, bool TA, bool TB, int WPS, int EDGE, typename 
 __global__ void __launch_bounds__(BM * BN / 64 * KW) __attribute__((amdgpu_waves_per_eu(WPS)))
 pam_gemm_dma_kernel(GemmParams p) {
     constexpr bool kKeepAddresses = WPS <= 2 || (WPS == 3 && !TA);
-    constexpr int KPG = dma_kpg(BM, BN, KW);   // k steps per group per chunk
+    // k steps per group per chunk (the step masks hold one bit per step of a
+    // chunk in each half of a 32-bit word).
+    constexpr int KPG = kChunkK;
     constexpr int BK = KPG * KW;
     constexpr int NTG = BM * BN / 64;
     constexpr int NT = NTG * KW;
@@ -624,12 +622,12 @@ extern PAM_DMA_SHAPE(uint16_t, 0);
 extern PAM_DMA_SHAPE(uint16_t, 1);
 extern PAM_DMA_SHAPE(uint16_t, 2);
 
-hipError_t launch_pam_gemm_dma(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
+hipError_t launch_pam_gemm(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
                                const GemmParams &p, hipStream_t stream) {
     const int64_t items = (int64_t)p.whole + (int64_t)p.split_tiles * p.splits;
     if (items <= 0 || items > kMaxLaunchItems)
         return hipErrorInvalidValue;
-    const int bk = dma_kpg(tile_m, tile_n, kgroups) * kgroups;
+    const int bk = kChunkK * kgroups;
     const int piece = bf16 ? 8 : 4;   // elements
     const bool cut = p.k % bk != 0 || (p.split_tiles > 0 && p.k_per_split % bk != 0) ||
                      (trans_a && p.m % piece != 0) || (!trans_b && p.n % piece != 0);

@@ -1,6 +1,6 @@
 // Internal interface between the C-ABI layer (pam_api.cpp) and the HIP
-// kernels (pam_gemm_dma.hip, pam_kernels.hip, pa_ops.hip,
-// pam_exact_grad.hip).  Not installed; not part of the public ABI.
+// kernels (pam_gemm_dma.hip, pam_skinny.hip, pam_small.hip, pam_kernels.hip,
+// pa_ops.hip, pam_exact_grad.hip).  Not installed; not part of the public ABI.
 #pragma once
 
 #include <stdint.h>
@@ -49,8 +49,10 @@ hipError_t launch_paexp2(const float *a, float *out, int64_t n, hipStream_t stre
 // Round to 23 - drop mantissa bits, nearest even (drop in [1, 23]).
 hipError_t launch_round_mantissa(const float *a, float *out, int64_t n, int drop, hipStream_t stream);
 
-// (tile_m, tile_n, kgroups) in {(128,128,1), (128,64,1), (64,64,1), (64,64,4)};
-// a one-dimensional grid of p.whole + p.split_tiles * p.splits workgroups.
+// The tiled product (pam_gemm_dma.hip): operand chunks copied into LDS by the
+// memory pipeline.  (tile_m, tile_n, kgroups) in {(128,128,1), (128,64,1),
+// (128,64,2), (64,64,1), (64,64,4)}; a one-dimensional grid of p.whole +
+// p.split_tiles * p.splits workgroups.
 // bf16: p.A and p.B hold bfloat16 elements (leading dimensions and strides
 // in elements), widened exactly to float32 as they are loaded.
 hipError_t launch_pam_gemm(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
@@ -87,11 +89,6 @@ hipError_t launch_pam_skinny(bool rows, bool bf16, const GemmParams &p, int64_t 
 // chunk's k steps.  One launch for the batch; takes no plan and no workspace.
 constexpr int kSmallWaves = 8;
 hipError_t launch_pam_small(bool trans_a, bool trans_b, bool bf16, GemmParams p, int64_t batch, hipStream_t stream);
-
-// The kernel behind launch_pam_gemm (pam_gemm_dma.hip): operand chunks
-// copied into LDS by the memory pipeline.
-hipError_t launch_pam_gemm_dma(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
-                               const GemmParams &p, hipStream_t stream);
 
 // C of the split tiles of a product launch: element by element the sum over s
 // of W[s][t][.][.], in an order fixed by the number of slices.

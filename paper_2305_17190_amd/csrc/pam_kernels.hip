@@ -1,8 +1,6 @@
-// Launch entry of the PAM matrix products (their kernel, for float32 and
-// bfloat16 operands, is pam_gemm_dma_kernel in pam_gemm_dma.hip), the
-// reductions that add the K slices of split-K plans in a fixed order, the
-// fill of k == 0 products, and the static split-K scratch of the entry point
-// that allocates nothing.
+// Beside the PAM matrix product kernels: the reduction that adds the K slices of
+// split-K plans in a fixed order, the fill of k == 0 products, and the static
+// split-K scratch of the entry point that allocates nothing.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -13,18 +11,6 @@
 #include "pam_internal.h"
 
 namespace pamk {
-
-// ---------------------------------------------------------------------------
-// PAM matrix products: the kernel is in pam_gemm_dma.hip
-// ---------------------------------------------------------------------------
-
-hipError_t launch_pam_gemm(int tile_m, int tile_n, int kgroups, bool trans_a, bool trans_b, bool bf16,
-                           const GemmParams &p, hipStream_t stream) {
-    const int64_t items = (int64_t)p.whole + (int64_t)p.split_tiles * p.splits;
-    if (items <= 0 || items > kMaxLaunchItems)
-        return hipErrorInvalidValue;
-    return launch_pam_gemm_dma(tile_m, tile_n, kgroups, trans_a, trans_b, bf16, p, stream);
-}
 
 // ---------------------------------------------------------------------------
 // Split-K reduction and k == 0 fill

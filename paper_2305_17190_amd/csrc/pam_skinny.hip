@@ -5,15 +5,19 @@
 // What bounds it: reading the wide operand once.  The tiled kernel pads the
 // few rows to 64 and gives each workgroup a few chunks between barriers.
 // Measured against it (one call after the other, other weights each time): 8
-// x 4096 x 4096 21.1 us (55.6; its 67 MB take 14 us at a copy's rate), 1 x 4096
-// x 4096 19.2 us (56.0), 16 x 4096 x 4096 27.6 us (56.7), 32 x 4096 x 4096
-// 51.4 us (55.3: two passes of 16 rows; the line is drawn there), 8 x 2048 x
-// 512 5.3 us (26.8), 32 x 768 x 192 6.0 us (19.7).  Here no wave waits for another until the end: a lane
-// holds four consecutive k of kJ rows of the wide operand, loaded straight
-// into registers one chunk ahead (16 lanes read 256 consecutive bytes of a
-// row), and keeps a sum for each of S skinny rows and its kJ wide rows; the
-// skinny operand's chunk comes from LDS, written by the wave itself.  The
-// waves of a workgroup take parts of K (long K) or further wide rows.
+// x 4096 x 4096 20.6 us (52.5; its 67 MB take 14 us at a copy's rate), 1 x 4096
+// x 4096 18.8 us (53.0), 16 x 4096 x 4096 25.9 us (53.9), 32 x 4096 x 4096
+// 47.9 us (54.1; two passes of 16 rows), 8 x 2048 x 512 4.9 us (27.7), 32 x 768 x
+// 192 6.0 us (20.7); bfloat16, 4096 x 4096 weights: 1 row 11.0 us (61.4), 8 rows
+// 14.9 us (61.7), 16 rows 22.5 us (62.1), 32 rows 43.6 us (62.1).  Where it is
+// taken: skinny_product in pam_api.cpp.
+//
+// No wave waits for another until the end: a lane holds four consecutive k of
+// kJ rows of the wide operand, loaded straight into registers one chunk ahead
+// (16 lanes read 256 consecutive bytes of a row), and keeps a sum for each of S
+// skinny rows and its kJ wide rows, folded into the outputs every kFoldChunks
+// chunks; the skinny operand's chunk comes from LDS, written by the wave
+// itself.  The waves of a workgroup take parts of K (long K) or further wide rows.
 //
 // Arithmetic: the SCALED form with the product and sum in one fma (S2 of
 // pam_gemm_dma.hip): t = (1 + M_x) + w' is the encoding of PAM(1 + M_x, w),

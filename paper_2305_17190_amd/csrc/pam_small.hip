@@ -17,11 +17,12 @@
 // own) when one is a tiny normal, the complete definition when one is inf,
 // NaN or |x| >= 2^64.
 //
-// Measured against the tiled kernel's plans: 256^3 7.0 us (25.4 us), 512 x 512
-// x 256 7.6 us (25.6), 1024 x 1024 x 256 19.4 us (26.5), 256 x 256 x 1024 19.0 us
-// (27.1), 128 x 128 x 64 5.6 us (10.7), 16 matrices of 197 x 64 x 197 9.0 us (25.7);
-// 2048 x 1024 x 256 34.9 us (27.8) and 128 x 128 x 4096 65 us (28.5, K in slices)
-// stay with the plan (small_product in pam_api.cpp).
+// Measured against the tiled kernel's plans: 256^3 6.9 us (26.7 us), 512 x 512
+// x 256 7.7 us (27.0), 1024 x 1024 x 256 19.2 us (27.3), 256 x 256 x 1024 19.1 us
+// (27.5), 128 x 128 x 64 5.2 us (10.9), 16 matrices of 197 x 197 x 64 11.7 us (13.4);
+// half-zero operands 256^3 8.2 us (36.8), 256 x 256 x 1024 25.1 us (35.6); 2048 x 1024
+// x 256 34.9 us (27.8) and 128 x 128 x 4096 65 us (28.5, K in slices) stay with the
+// plan (small_product in pam_api.cpp).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
